@@ -289,27 +289,32 @@ def run(state):
 
 
 def _selected(case, n, mean):
-    """A segment of ``n`` clusters drawn small and on the host, by the recipe of the inputs: (clusters some head of
-    the group takes exactly, clusters some head only approximates, rows summed over the heads)."""
+    """The segments of a sequence with ``n`` clusters, drawn again on the host by the recipe of the inputs: (clusters
+    that some head of a group takes exactly, clusters that heads only approximate, rows summed over the heads), of
+    all its KV heads together."""
     rng = np.random.default_rng(5)
-    centres = 2.0 * rng.standard_normal((n, DIM), dtype=np.float32)
-    scale = _scales(case, rng)
-    exact, kept, rows = np.zeros(n, bool), np.zeros(n, bool), 0
-    for j in range(case["group"]):
-        aim = (rng.dirichlet(np.ones(4))[:, None] * scale(j) * centres[rng.integers(0, n, 4)]).sum(0)
-        x = centres @ (aim + rng.standard_normal(DIM)).astype(np.float32) / math.sqrt(DIM)
-        order = np.argsort(-x)
-        w = np.exp(x[order] - x.max())
-        mass = np.cumsum(w) / w.sum()
-        if case["kind"] == "budget":
-            n1, n2 = max(1, int(case["keep"] * n)), max(1, int(case["exact"] * n))
-        else:
-            n1 = int(np.searchsorted(mass, case["p1"])) + 1
-            n2 = int(np.searchsorted(mass, case["p2"] * mass[min(n1, n) - 1])) + 1
-        exact[order[:n2]] = True
-        kept[order[:n1]] = True
-        rows += n2 * mean + n1 - n2
-    return int(exact.sum()), int((kept & ~exact).sum()), rows
+    n_exact = n_approx = n_rows = 0
+    for g in range(case["kv_heads"]):
+        centres = 2.0 * rng.standard_normal((n, DIM), dtype=np.float32)
+        scale = _scales(case, rng)
+        exact, kept = np.zeros(n, bool), np.zeros(n, bool)
+        for h in range(g * case["group"], (g + 1) * case["group"]):
+            aim = (rng.dirichlet(np.ones(4))[:, None] * scale(h) * centres[rng.integers(0, n, 4)]).sum(0)
+            x = centres @ (aim + rng.standard_normal(DIM)).astype(np.float32) / math.sqrt(DIM)
+            order = np.argsort(-x)
+            w = np.exp(x[order] - x.max())
+            mass = np.cumsum(w) / w.sum()
+            if case["kind"] == "budget":
+                n1, n2 = max(1, int(case["keep"] * n)), max(1, int(case["exact"] * n))
+            else:
+                n1 = int(np.searchsorted(mass, case["p1"])) + 1
+                n2 = int(np.searchsorted(mass, case["p2"] * mass[min(n1, n) - 1])) + 1
+            exact[order[:n2]] = True
+            kept[order[:n1]] = True
+            n_rows += n2 * mean + n1 - n2
+        n_exact += int(exact.sum())
+        n_approx += int((kept & ~exact).sum())
+    return n_exact, n_approx, n_rows
 
 
 def work(case):
@@ -328,12 +333,15 @@ def work(case):
     if case["kind"] == "dense":
         return {"bytes": tokens * 2 * ROW + ends, "flops": 4.0 * DIM * tokens * case["group"]}
     nbytes = flops = 0.0
+    seen = {}
     for n, m in zip(ctx, ncl):
-        exact, approx, rows = _selected(case, m, n / m)
+        if m not in seen:
+            seen[m] = _selected(case, m, n / m)
+        exact, approx, rows = seen[m]
         if case["pinned"]:
-            exact, rows = exact + 5, rows + 5 * case["group"] * n / m
-        nbytes += kvh * (m * (ROW + 4) + (exact * n / m + approx) * 2 * ROW)
-        flops += kvh * (2.0 * DIM * m * case["group"] + 4.0 * DIM * rows)
+            exact, rows = exact + 5 * kvh, rows + 5 * kvh * case["group"] * n / m
+        nbytes += kvh * m * (ROW + 4) + (exact * n / m + approx) * 2 * ROW
+        flops += kvh * 2.0 * DIM * m * case["group"] + 4.0 * DIM * rows
     return {"bytes": case["layers"] * (nbytes + ends), "flops": case["layers"] * flops}
 
 
