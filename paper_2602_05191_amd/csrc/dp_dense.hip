@@ -23,10 +23,16 @@
 // rescaling of the accumulators is lane-local; it is skipped while no maximum moves.
 // Matrix-core time per 16 rows: 4 x 16 + 32 x 32 cycles, whatever the group size is:
 // 29 us at 2.4 GHz for the million rows of 8 x 131072 tokens, behind 87 us of HBM
-// time at 6.2 TB/s.  Measured there at G = 4: 94.5 us = 5.7 TB/s (108 us with the dot
-// products, G softmaxes per row in 16 lanes each and G x 128 multiply-adds per row on
-// the vector ALU; that form was vector-bound at G = 8).  The per-split partials (m, l, acc[128]) are merged
-// by a second small kernel: no counters, no atomics.
+// time at 6.2 TB/s.  Measured there at G = 4: 82 us = 6.5 TB/s with non-temporal
+// loads, 94.5 us = 5.7 TB/s with plain ones (108 us with the dot products, G softmaxes
+// per row in 16 lanes each and G x 128 multiply-adds per row on the vector ALU; that form
+// was vector-bound at G = 8).
+// Work split: the segments' rows, in chunks of 64, are dealt out evenly to one round of
+// resident workgroups, whatever the lengths of the segments (the lengths are on the
+// device: every workgroup derives its own share from them).  A share may end one segment
+// and begin the next (three segments of 24 to 45 k tokens x 8 KV heads, G = 8: 83 -> 73.5
+// us against equal ranges of the longest segment).  The partials (m, l, acc[128]) of the pieces of a segment are
+// merged by a second small kernel: no counters, no atomics.
 #include "dp_attend.hpp"
 #include "dp_device.hpp"
 #include "dp_kernels.hpp"
@@ -48,11 +54,42 @@ struct DenseArgs {
   const int64_t *seg_row_base;
   const int32_t *seg_rows;
   float *partials;  // [nh, splits, kPartialStride]
-  int32_t n_kv_heads, n_q_heads, group;
+  void *out;
+  float *lse;  // nullable
+  int32_t n_seg, n_kv_heads, n_q_heads, group;
   int32_t head0;  // this launch serves heads [head0, head0 + 16) of every group
-  int32_t splits, rows_per_split, max_rows;
+  int32_t splits, min_share, grid, max_rows, out_is_bf16;
   float scale_log2;
 };
+
+// How the chunks (kChunkRows rows) of all segments, numbered through in segment order, are dealt out: workgroup w
+// takes chunks [w share, (w + 1) share).
+struct DenseShare {
+  int total, share;
+};
+
+// Call with the whole workgroup of T threads; s_scan: T / 64 + 1 ints of LDS.  find(seg, first chunk, chunks of seg) is
+// called once for every segment that has rows, each by some thread.
+template <int T, class F>
+__device__ __forceinline__ DenseShare dense_share(const DenseArgs &a, int *s_scan, F find) {
+  const int per = (a.n_seg + T - 1) / T;  // consecutive segments per thread
+  int mine = 0;
+  for (int u = 0; u < per; ++u) {
+    const int seg = threadIdx.x * per + u;
+    if (seg < a.n_seg) mine += (max(0, min(a.seg_rows[seg], a.max_rows)) + kChunkRows - 1) / kChunkRows;
+  }
+  DenseShare d;
+  int run = block_excl_scan<int, T / 64>(mine, s_scan, d.total);
+  d.share = max(a.min_share, (d.total + a.grid - 1) / a.grid);
+  for (int u = 0; u < per; ++u) {
+    const int seg = threadIdx.x * per + u;
+    if (seg >= a.n_seg) break;
+    const int chunks = (max(0, min(a.seg_rows[seg], a.max_rows)) + kChunkRows - 1) / kChunkRows;
+    if (chunks > 0) find(seg, run, chunks, d.share);
+    run += chunks;
+  }
+  return d;
+}
 
 // one wave's 16 cache rows as the two contractions want them
 struct DenseTile {
@@ -60,152 +97,174 @@ struct DenseTile {
 };
 
 // Rows beyond the range read its last row: a lane's loads never leave the segment, and their weight is zero.
+// (row0 and t are uniform in the wave: the tile's base is a scalar, a lane adds a 32-bit offset.)
 __device__ __forceinline__ void load_dense_tile(const DenseArgs &a, int64_t row0, int t, int last, int r, int kq,
                                                 DenseTile &d) {
-  const char *k = static_cast<const char *>(a.k_cache) + (row0 + min(t + r, last)) * kRowBytes + kq * 16;
+  const int base = min(t, last), more = last - base;
+  const char *k = static_cast<const char *>(a.k_cache) + (row0 + base) * kRowBytes;
+  const char *v = static_cast<const char *>(a.v_cache) + (row0 + base) * kRowBytes;
+  const uint32_t ko = (uint32_t)min(r, more) * kRowBytes + kq * 16;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) d.k[j] = *reinterpret_cast<const uint4 *>(k + j * 64);
+  for (int j = 0; j < 4; ++j) d.k[j] = load_stream16(k + (ko + j * 64));
 #pragma unroll
-  for (int i = 0; i < 4; ++i) d.v[i] = load_row_slice(a.v_cache, row0 + min(t + 4 * kq + i, last), r);
+  for (int i = 0; i < 4; ++i) d.v[i] = load_stream16(v + ((uint32_t)min(4 * kq + i, more) * kRowBytes + r * 16));
 }
 
-__global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void dense_kernel(DenseArgs a) {
+__global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void dense_kernel(DenseArgs a) {
   __shared__ float s_m[kDenseWaves][kDenseHeads], s_l[kDenseWaves][kDenseHeads];
   __shared__ __align__(16) float s_acc[kDenseWaves][kDenseHeads][kHeadDim + 4];
-  const int seg = blockIdx.y, split = blockIdx.x;
-  const int R = min(a.seg_rows[seg], a.max_rows);
-  const int ra = split * a.rows_per_split;
-  const int rb = min(R, ra + a.rows_per_split);
-  if (ra >= rb) return;  // the merge kernel derives the number of live splits from R as well
-
-  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  __shared__ int s_scan[kDenseWaves + 1], s_seg, s_first;
+  const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
   const int r = lane & 15, kq = lane >> 4;
-  const int b = seg / a.n_kv_heads, g = seg % a.n_kv_heads;
-  const int64_t head_first = (int64_t)b * a.n_q_heads + g * a.group + a.head0;
-  const int n_live = min(kDenseHeads, a.group - a.head0);
-  const int64_t row0 = a.seg_row_base[seg];
-
-  // query head r of the pass (a zero column beyond the group), chunks kq + 4 j
-  uint4 Q[4];
-  {
-    const char *row = static_cast<const char *>(a.q) + (head_first + min(r, n_live - 1)) * kRowBytes + kq * 16;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) Q[j] = r < n_live ? *reinterpret_cast<const uint4 *>(row + j * 64) : make_uint4(0, 0, 0, 0);
-  }
-  f32x4 acc[8];
-#pragma unroll
-  for (int n = 0; n < 8; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;  // head r: the maximum of all rows so far, the weights of this lane's rows
-
-  auto attend = [&](const DenseTile &d, int t) {
-    f32x4 x = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, d.k[j]), __builtin_bit_cast(bf16x8, Q[j]),
-                                                  x, 0, 0, 0);
-    float top = m;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[i] = t + 4 * kq + i < rb ? x[i] * a.scale_log2 : -INFINITY;
-      top = fmaxf(top, x[i]);
+  const DenseShare dealt = dense_share<kDenseThreads>(a, s_scan, [&](int seg, int first, int chunks, int share) {
+    const int c = blockIdx.x * share;
+    if (first <= c && c < first + chunks) {  // the segment that holds the first chunk of this workgroup
+      s_seg = seg;
+      s_first = first;
     }
-    top = fmaxf(top, xor16(top));
-    top = fmaxf(top, xor32(top));
-    if (__ballot(top > m)) {  // finite from the first tile on: its first row is inside the range
-      const float alpha = __builtin_amdgcn_exp2f(m - top);
-      l *= alpha;
-#pragma unroll
-      for (int n = 0; n < 8; ++n) acc[n] *= alpha;
-      m = top;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[i] = __builtin_amdgcn_exp2f(x[i] - m);
-      l += x[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float v[8];
-      unpack8(d.v[i], v);
-#pragma unroll
-      for (int n = 0; n < 8; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[n], x[i], acc[n], 0, 0, 0);
-    }
-  };
-
-  // the workgroup's waves take tiles in turn; the next tile's loads are in flight during a tile's arithmetic
-  constexpr int kStep = kDenseWaves * kDenseTile;
-  int t = ra + wave * kDenseTile;
-  if (t < rb) {
-    DenseTile d0, d1;
-    load_dense_tile(a, row0, t, rb - 1, r, kq, d0);
-    while (true) {
-      load_dense_tile(a, row0, t + kStep, rb - 1, r, kq, d1);
-      attend(d0, t);
-      t += kStep;
-      if (t >= rb) break;
-      load_dense_tile(a, row0, t + kStep, rb - 1, r, kq, d0);
-      attend(d1, t);
-      t += kStep;
-      if (t >= rb) break;
-    }
-  }
-  l += xor16(l);
-  l += xor32(l);
-
-  // merge the waves through LDS: lane (r, kq) holds dims 8 (4 kq + i) + n of head r
-  if (r < n_live) {
-    if (kq == 0) {
-      s_m[wave][r] = m;
-      s_l[wave][r] = l;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float4 *dst = reinterpret_cast<float4 *>(&s_acc[wave][r][8 * (4 * kq + i)]);
-      dst[0] = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-      dst[1] = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
-    }
-  }
+  });
+  int c0 = blockIdx.x * dealt.share;
+  const int c_end = min(dealt.total, c0 + dealt.share);
+  if (c0 >= c_end) return;
   __syncthreads();
-  // thread t: dim t % 128 of heads t / 128, t / 128 + 2, ...
-  for (int j = tid / kHeadDim; j < n_live; j += kDenseThreads / kHeadDim) {
-    const int d = tid % kHeadDim;
-    float M = -INFINITY, L = 0.f, o = 0.f;
+  int seg = s_seg, first = s_first;
+  const int n_live = min(kDenseHeads, a.group - a.head0);
+
+  // one piece of a segment after the other, usually one
+  for (; c0 < c_end; ++seg) {
+    const int R = max(0, min(a.seg_rows[seg], a.max_rows));
+    if (R == 0) continue;
+    const int seg_end = first + (R + kChunkRows - 1) / kChunkRows;
+    const int ra = (c0 - first) * kChunkRows, rb = min(R, (min(c_end, seg_end) - first) * kChunkRows);
+    const int split = blockIdx.x - first / dealt.share;  // number of the piece inside its segment
+    c0 = seg_end;
+    first = seg_end;
+    const int b = seg / a.n_kv_heads, g = seg % a.n_kv_heads;
+    const int64_t head_first = (int64_t)b * a.n_q_heads + g * a.group + a.head0;
+    const int64_t row0 = a.seg_row_base[seg];
+
+    // query head r of the pass (a zero column beyond the group), chunks kq + 4 j
+    uint4 Q[4];
+    {
+      const char *row = static_cast<const char *>(a.q) + (head_first + min(r, n_live - 1)) * kRowBytes + kq * 16;
 #pragma unroll
-    for (int w = 0; w < kDenseWaves; ++w) M = fmaxf(M, s_m[w][j]);
+      for (int j = 0; j < 4; ++j)
+        Q[j] = r < n_live ? *reinterpret_cast<const uint4 *>(row + j * 64) : make_uint4(0, 0, 0, 0);
+    }
+    f32x4 acc[8];
 #pragma unroll
-    for (int w = 0; w < kDenseWaves; ++w) {
-      const float wg = (s_m[w][j] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s_m[w][j] - M);
-      L += s_l[w][j] * wg;
-      o += s_acc[w][j][d] * wg;
+    for (int n = 0; n < 8; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;  // head r: the maximum of all rows so far, the weights of this lane's rows
+
+    auto attend = [&](const DenseTile &d, int t) {
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, d.k[j]),
+                                                    __builtin_bit_cast(bf16x8, Q[j]), x, 0, 0, 0);
+      float top = m;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[i] = t + 4 * kq + i < rb ? x[i] * a.scale_log2 : -INFINITY;
+        top = fmaxf(top, x[i]);
+      }
+      top = fmaxf(top, xor16(top));
+      top = fmaxf(top, xor32(top));
+      if (__ballot(top > m)) {  // finite from the first tile on: its first row is inside the range
+        const float alpha = __builtin_amdgcn_exp2f(m - top);
+        l *= alpha;
+#pragma unroll
+        for (int n = 0; n < 8; ++n) acc[n] *= alpha;
+        m = top;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[i] = __builtin_amdgcn_exp2f(x[i] - m);
+        l += x[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float v[8];
+        unpack8(d.v[i], v);
+#pragma unroll
+        for (int n = 0; n < 8; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[n], x[i], acc[n], 0, 0, 0);
+      }
+    };
+
+    // the workgroup's waves take tiles in turn; the next tile's loads are in flight during a tile's arithmetic
+    constexpr int kStep = kDenseWaves * kDenseTile;
+    int t = ra + wave * kDenseTile;
+    if (t < rb) {
+      DenseTile d0, d1;
+      load_dense_tile(a, row0, t, rb - 1, r, kq, d0);
+      while (true) {
+        load_dense_tile(a, row0, t + kStep, rb - 1, r, kq, d1);
+        attend(d0, t);
+        t += kStep;
+        if (t >= rb) break;
+        load_dense_tile(a, row0, t + kStep, rb - 1, r, kq, d0);
+        attend(d1, t);
+        t += kStep;
+        if (t >= rb) break;
+      }
     }
-    float *P = a.partials + ((head_first + j) * a.splits + split) * kPartialStride;
-    if (d == 0) {
-      P[0] = M;
-      P[1] = L;
+    l += xor16(l);
+    l += xor32(l);
+
+    // merge the waves through LDS: lane (r, kq) holds dims 8 (4 kq + i) + n of head r
+    if (r < n_live) {
+      if (kq == 0) {
+        s_m[wave][r] = m;
+        s_l[wave][r] = l;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float4 *dst = reinterpret_cast<float4 *>(&s_acc[wave][r][8 * (4 * kq + i)]);
+        dst[0] = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
+        dst[1] = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
+      }
     }
-    P[2 + d] = o;
+    __syncthreads();
+    // thread t: dim t % 128 of heads t / 128, t / 128 + 2, ...
+    for (int j = tid / kHeadDim; j < n_live; j += kDenseThreads / kHeadDim) {
+      const int d = tid % kHeadDim;
+      float M = -INFINITY, L = 0.f, o = 0.f;
+#pragma unroll
+      for (int w = 0; w < kDenseWaves; ++w) M = fmaxf(M, s_m[w][j]);
+#pragma unroll
+      for (int w = 0; w < kDenseWaves; ++w) {
+        const float wg = (s_m[w][j] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s_m[w][j] - M);
+        L += s_l[w][j] * wg;
+        o += s_acc[w][j][d] * wg;
+      }
+      float *P = a.partials + ((head_first + j) * a.splits + split) * kPartialStride;
+      if (d == 0) {
+        P[0] = M;
+        P[1] = L;
+      }
+      P[2 + d] = o;
+    }
+    __syncthreads();  // LDS is reused by the next piece
   }
 }
-
-struct DenseMergeArgs {
-  const float *partials;
-  const int32_t *seg_rows;
-  void *out;
-  float *lse;  // nullable
-  int32_t n_kv_heads, n_q_heads, group, splits, rows_per_split, max_rows, out_is_bf16;
-};
 
 // One workgroup per head; its eight groups of 128 threads (one dimension each) take the splits in turn, so that the
 // partials of a head are fetched in a round or two of loads, and meet in LDS.  (One group walking all splits of a head
 // eight at a time took 20 us for the 96 splits of 8 x 131072 tokens: a dozen dependent round trips on 32 CUs.)
 constexpr int kMergeGroups = 8;
-__global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(DenseMergeArgs a) {
+__global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(DenseArgs a) {
   __shared__ float s_m[kMergeGroups], s_l[kMergeGroups], s_o[kMergeGroups][kHeadDim];
+  __shared__ int s_scan[kMergeGroups * kHeadDim / 64 + 1], s_pieces;
   const int head = blockIdx.x, t = threadIdx.x % kHeadDim, grp = threadIdx.x / kHeadDim;
   const int b = head / a.n_q_heads, h = head % a.n_q_heads;
-  const int seg = b * a.n_kv_heads + h / a.group;
-  const int R = min(a.seg_rows[seg], a.max_rows);
-  const int n_active = (R + a.rows_per_split - 1) / a.rows_per_split;
+  const int my_seg = b * a.n_kv_heads + h / a.group;
+  if (threadIdx.x == 0) s_pieces = 0;
+  __syncthreads();
+  dense_share<kMergeGroups * kHeadDim>(a, s_scan, [&](int seg, int first, int chunks, int share) {
+    if (seg == my_seg) s_pieces = (first + chunks - 1) / share - first / share + 1;
+  });
+  __syncthreads();
+  const int n_active = s_pieces;
   if (n_active <= 0) {  // an empty segment: zero output
     if (grp > 0) return;
     store_out(a.out, a.out_is_bf16, head, t, 0.f);
@@ -227,7 +286,7 @@ __global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(De
     float Mn = Mx;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (s0 + kMergeGroups * u >= n_active) ms[u] = -INFINITY;  // every live split has at least one row: its m is finite
+      if (s0 + kMergeGroups * u >= n_active) ms[u] = -INFINITY;  // (a live split's m is finite)
       Mn = fmaxf(Mn, ms[u]);
     }
     const float sc = __builtin_amdgcn_exp2f(Mx - Mn);
@@ -263,62 +322,49 @@ __global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(De
 
 }  // namespace
 
-// Equal row ranges stream at equal speed, so the grid is ONE round of workgroups: as many as are resident
-// at once (three waves per SIMD x 256 CUs), each with at least 256 rows (four steps).
-void dense_split(int max_rows, int n_seg, int max_splits, int *splits, int *rows_per_split) {
-  constexpr int resident = 3 * 256;
-  long want = resident / n_seg;
-  if (want > max_splits) want = max_splits;
-  const long by_rows = ((long)max_rows + 255) / 256;
-  if (want > by_rows) want = by_rows;
-  if (want < 1) want = 1;
-  const long c = kChunkRows * (((long)max_rows + kChunkRows * want - 1) / (kChunkRows * want));
-  *rows_per_split = (int)(c > 0 ? c : kChunkRows);
-  *splits = (int)(((long)max_rows + *rows_per_split - 1) / *rows_per_split);
-  if (*splits < 1) *splits = 1;
-}
-
 hipError_t launch_dense(const CacheView &c, const int32_t *seg_rows, float *partials, int max_splits,
                         const AttnOut &attn, hipStream_t s) {
   const int n_seg = c.batch * c.n_kv_heads, nh = c.batch * c.n_q_heads;
   if (nh == 0) return hipSuccess;
-  int splits, rows_per_split;
-  dense_split(c.max_rows_per_seg, n_seg, max_splits, &splits, &rows_per_split);
+  DenseArgs a;
+  a.q = c.q;
+  a.k_cache = c.k_cache;
+  a.v_cache = c.v_cache;
+  a.seg_row_base = c.seg_row_base;
+  a.seg_rows = seg_rows;
+  a.partials = partials;
+  a.out = attn.out;
+  a.lse = attn.lse;
+  a.out_is_bf16 = attn.out_is_bf16;
+  a.n_seg = n_seg;
+  a.n_kv_heads = c.n_kv_heads;
+  a.n_q_heads = c.n_q_heads;
+  a.group = c.group;
+  a.head0 = 0;
+  a.splits = max_splits;
+  a.max_rows = c.max_rows_per_seg;
+  a.scale_log2 = c.sm_scale * kLog2e;
+  // One round of workgroups: as many as are resident at once (two waves per SIMD x 256 CUs; at three waves per SIMD
+  // the next tile's registers spill: 113 against 86 us over 8 x 131072 tokens).  A small call is cut down to one step
+  // per workgroup (2 x 3001 tokens: 11.1 us, 13.9 with at least four steps each; no difference on large calls).
+  // A segment of n chunks has at most ceil(n / share) + 1 pieces, and never more than n: the share is large enough for
+  // the partial slots of a head.
+  constexpr int kResident = 2 * 256;
+  const int max_chunks = (c.max_rows_per_seg + kChunkRows - 1) / kChunkRows;
+  a.min_share = 1;
+  if (max_chunks > max_splits && max_splits > 1) {
+    const int least = (max_chunks + max_splits - 2) / (max_splits - 1);
+    if (a.min_share < least) a.min_share = least;
+  }
+  const long want = ((long)n_seg * max_chunks + a.min_share - 1) / a.min_share;
+  a.grid = (int)(want < 1 ? 1 : want < kResident ? want : kResident);
   if (c.max_rows_per_seg > 0) {
-    DenseArgs a;
-    a.q = c.q;
-    a.k_cache = c.k_cache;
-    a.v_cache = c.v_cache;
-    a.seg_row_base = c.seg_row_base;
-    a.seg_rows = seg_rows;
-    a.partials = partials;
-    a.n_kv_heads = c.n_kv_heads;
-    a.n_q_heads = c.n_q_heads;
-    a.group = c.group;
-    a.splits = splits;
-    a.rows_per_split = rows_per_split;
-    a.max_rows = c.max_rows_per_seg;
-    a.scale_log2 = c.sm_scale * kLog2e;
-    const dim3 grid(splits, n_seg);
-    // one pass over the cache for up to 16 heads of a group
-    for (int h0 = 0; h0 < c.group; h0 += kDenseHeads) {
+    for (int h0 = 0; h0 < c.group; h0 += kDenseHeads) {  // one pass over the cache for up to 16 heads of a group
       a.head0 = h0;
-      hipLaunchKernelGGL(dense_kernel, grid, dim3(kDenseThreads), 0, s, a);
+      hipLaunchKernelGGL(dense_kernel, dim3(a.grid), dim3(kDenseThreads), 0, s, a);
     }
   }
-  DenseMergeArgs m;
-  m.partials = partials;
-  m.seg_rows = seg_rows;
-  m.out = attn.out;
-  m.lse = attn.lse;
-  m.n_kv_heads = c.n_kv_heads;
-  m.n_q_heads = c.n_q_heads;
-  m.group = c.group;
-  m.splits = splits;
-  m.rows_per_split = rows_per_split;
-  m.max_rows = c.max_rows_per_seg;
-  m.out_is_bf16 = attn.out_is_bf16;
-  hipLaunchKernelGGL(dense_merge_kernel, dim3(nh), dim3(kMergeGroups * kHeadDim), 0, s, m);
+  hipLaunchKernelGGL(dense_merge_kernel, dim3(nh), dim3(kMergeGroups * kHeadDim), 0, s, a);
   return hipGetLastError();
 }
 

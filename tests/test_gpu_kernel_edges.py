@@ -21,3 +21,19 @@ def test_dense_decode_at_tile_and_split_edges(n_q_heads):
     # scores' own rounding times their size (|x| <= 40: 40 x 2^-23) above it
     assert np.abs(out - ref).max() <= 2e-5
     assert np.abs(lse - ref_lse).max() <= 2e-5 * np.abs(ref_lse).max()
+
+
+def test_dense_decode_deals_rows_out_over_ragged_segments():
+    """Shares of 64-row chunks that end one segment and begin the next, empty segments between them, and (512 heads: 32
+    partial slots each) a segment with more chunks than slots."""
+    ctx = [4000, 1, 700, 64, 2500, 65, 3000, 128]
+    c = make_cache(batch=len(ctx), n_kv_heads=4, n_q_heads=64, context=ctx, mean_cluster=16, q_scale=0.7, seed=62)
+    rows = H.segment_rows(c)
+    rows[[5, 6, 30]] = 0   # these heads attend to nothing
+    out, lse = H.gpu_dense_decode(c, rows)
+    ref, ref_lse, _ = oracle.Oracle(c).dense_step(n_threads=4)
+    empty = np.repeat(rows == 0, 16).reshape(out.shape[:2])
+    assert (out[empty] == 0).all() and np.isneginf(lse[empty]).all()
+    # as above; 4000 rows
+    assert np.abs(out - ref)[~empty].max() <= 2e-5
+    assert np.abs(lse - ref_lse)[~empty].max() <= 2e-5 * np.abs(ref_lse).max()
