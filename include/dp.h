@@ -284,7 +284,7 @@ typedef struct {
 } dp_prefill;
 
 /* Host-only.  Device workspace dp_build_cluster_cache needs (per segment and
- * 1024-token block one int32 per cluster, plus 6 bytes per token); 0 for an
+ * 4096-token block one int32 per 16 clusters, plus 14 bytes per token); 0 for an
  * invalid description. */
 size_t dp_build_workspace_bytes(const dp_prefill *in);
 

@@ -499,10 +499,7 @@ static bool prefill_ok(const dp_prefill *in) {
 
 size_t dp_build_workspace_bytes(const dp_prefill *in) {
   if (!prefill_ok(in)) return 0;
-  size_t hist, rank, row_token;
-  int nb;
-  dp::build_workspace_layout(in->n_seg, in->max_rows_per_seg, in->max_clusters_per_seg, &hist, &rank, &row_token, &nb);
-  return hist + rank + row_token;
+  return dp::build_workspace_bytes(in->n_seg, in->max_rows_per_seg, in->max_clusters_per_seg);
 }
 
 dp_status dp_build_cluster_cache(const dp_prefill *in, void *k_cache, void *v_cache, int32_t *cluster_offsets,
@@ -510,7 +507,7 @@ dp_status dp_build_cluster_cache(const dp_prefill *in, void *k_cache, void *v_ca
                                  int32_t *token_row, void *workspace, size_t workspace_bytes, void *stream) {
   if (!prefill_ok(in)) return DP_ERR_INVALID_ARG;
   if (in->head_dim != dp::kHeadDim) return DP_ERR_UNSUPPORTED;
-  // the per-block cluster counts of the sort live in LDS; the bound is the one the decode step has as well
+  // the per-block counts of the sort live in LDS; the bound is the one the decode step has as well
   if (in->max_clusters_per_seg > dp::kSelectMaxClusters) return DP_ERR_UNSUPPORTED;
   if (in->n_seg == 0) return DP_OK;
   if (!in->seg_row_base || !in->seg_rows || !in->seg_cluster_ptr) return DP_ERR_INVALID_ARG;
@@ -576,9 +573,8 @@ dp_status dp_kmeans_assign(const dp_prefill *in, const void *centroids, int32_t 
 
 size_t dp_kmeans_fit_workspace_bytes(const dp_prefill *in) {
   if (!prefill_ok(in)) return 0;
-  const size_t step = dp_kmeans_workspace_bytes(in) > dp_build_workspace_bytes(in) ? dp_kmeans_workspace_bytes(in)
-                                                                                    : dp_build_workspace_bytes(in);
-  return step + 2 * align_up(sizeof(int32_t) * (size_t)in->total_clusters, 256);
+  return dp_kmeans_workspace_bytes(in) > dp_build_workspace_bytes(in) ? dp_kmeans_workspace_bytes(in)
+                                                                       : dp_build_workspace_bytes(in);
 }
 
 // Lloyd's iteration on one stream: assignment (matrix cores), then the means of the keys per cluster through the
@@ -596,10 +592,6 @@ dp_status dp_kmeans_fit(const dp_prefill *in, void *centroids, int32_t n_iters, 
   if (workspace_bytes < need) return DP_ERR_WORKSPACE_TOO_SMALL;
   if (need > 0 && (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256)) return DP_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t counts = align_up(sizeof(int32_t) * (size_t)in->total_clusters, 256);
-  char *ws = static_cast<char *>(workspace);
-  int32_t *sizes = reinterpret_cast<int32_t *>(ws + need - 2 * counts);
-  int32_t *offsets = reinterpret_cast<int32_t *>(ws + need - counts);
 
   dp::KmeansProblem k;
   k.n_seg = in->n_seg;
@@ -626,12 +618,10 @@ dp_status dp_kmeans_fit(const dp_prefill *in, void *centroids, int32_t n_iters, 
   b.max_kc = in->max_clusters_per_seg;
   b.max_rows = in->max_rows_per_seg;
   b.k_centroids = centroids;  // cache pointers null: keys only, nothing moved
-  b.cluster_offsets = offsets;
-  b.cluster_sizes = sizes;
   if (in->max_rows_per_seg == 0) return DP_OK;  // no tokens anywhere: nothing to assign, every centroid stays
   for (int it = 0; it < n_iters; ++it) {
-    if (dp::launch_kmeans_assign(k, reinterpret_cast<float *>(ws), s) != hipSuccess) return DP_ERR_HIP;
-    if (dp::launch_build(b, ws, s) != hipSuccess) return DP_ERR_HIP;
+    if (dp::launch_kmeans_assign(k, static_cast<float *>(workspace), s) != hipSuccess) return DP_ERR_HIP;
+    if (dp::launch_build(b, workspace, s) != hipSuccess) return DP_ERR_HIP;
   }
   return DP_OK;
 }

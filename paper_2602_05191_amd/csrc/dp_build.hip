@@ -10,20 +10,25 @@
 // place inside its cluster is its token order, and the means are fp64 sums
 // taken in row order and rounded once to bf16.
 //
-//   rank     per 1024-token block: the block's count of every cluster (integer
-//            atomics on a table in LDS, written out as one row) and a token's
-//            rank among the EARLIER tokens of its block with the same id: 0 when
-//            the token is alone with its id in the block (the common case), else
-//            by pairwise compare among the tokens that are not
-//   scan     per cluster: exclusive prefix of those counts over the blocks
-//            (in place) and the cluster's size
-//   offsets  per segment: exclusive prefix of the sizes
-//   place    row of a token = offset of its cluster + count of its cluster in
-//            earlier blocks + rank; written per token (token_row) and, inverted,
-//            per row (the token that fills it)
-//   move     a workgroup per 16 clusters walks their rows (one contiguous run) in
-//            chunks: fetches each row's token, stores it in place, and sums the
-//            chunk's rows column by column from a copy in LDS
+// The sort has two levels, so that its tables stay small: tokens are first put
+// into bins of 16 consecutive clusters, in token order; the workgroup that moves a
+// bin then orders the bin's tokens (some hundreds) by cluster itself.
+//   rank     per 4096-token block: a token's rank among the earlier tokens of its
+//            block in the same bin, and the block's count of every bin
+//   scan     per segment: exclusive prefix of those counts over the blocks, and
+//            of the bins' totals
+//   place    position of a token = start of its bin + its bin's count in earlier
+//            blocks + rank: the token's number and cluster go there
+//   move     a workgroup per bin orders the bin's tokens by cluster, walks the rows
+//            (one contiguous run of the cache) in chunks, fetches each row's token,
+//            stores it in place, and sums the chunk's rows column by column from a
+//            copy in LDS
+// A lane finds the earlier tokens of its bin (its cluster) inside its wave from one
+// ballot per bit of the id; a wave takes its tokens in order and keeps a count of its
+// own per bin.  So the cost does not depend on how the ids are distributed.
+// (One level with a count per 1024-token block and cluster needed 33 MB of counts for
+// 8 x 131072 tokens and 8192 clusters, and compared tokens of equal id pairwise: 64 us in
+// four kernels in front of the move; the three kernels here take 27.)
 // The update step of k-means (mean key of every cluster, nothing moved) is the same
 // sequence with the cache pointers left null: the last kernel then fetches keys only and stores no row.
 #include "dp_device.hpp"
@@ -32,7 +37,10 @@
 namespace dp {
 namespace {
 
-constexpr int kBuildBlock = 1024;  // tokens per block = threads per workgroup of rank / scatter
+constexpr int kRankThreads = 1024, kRankWaves = kRankThreads / 64;
+constexpr int kRankRounds = 4;                            // tokens per thread
+constexpr int kBuildBlock = kRankThreads * kRankRounds;  // tokens per workgroup of the rank kernel
+constexpr int kBinClusters = 16;
 
 struct BuildArgs {
   const void *k_tokens, *v_tokens;
@@ -40,84 +48,122 @@ struct BuildArgs {
   const int64_t *seg_row_base;
   const int32_t *seg_rows, *seg_cluster_ptr;
   void *k_cache, *v_cache, *k_centroids, *v_centroids;
-  int32_t *cluster_offsets, *cluster_sizes, *token_row;  // token_row nullable
+  int32_t *cluster_offsets, *cluster_sizes, *token_row;  // all nullable
   float *v_sums;                                         // nullable
-  int32_t *hist;                                         // [n_seg, n_blocks, max_kc]
+  int32_t *hist;                                         // [n_seg, n_blocks, bin_stride]
   uint16_t *rank;                                        // [n_seg, n_blocks * kBuildBlock]
-  int32_t *row_token;                                    // [n_seg, max_rows]: segment-relative token of each cache row
-  int32_t n_blocks, max_kc, max_rows;
+  int32_t *bin_start;                                    // [n_seg, bin_stride + 1]
+  uint64_t *binned;                                      // [n_seg, max_rows]: 16 x token + cluster of the bin
+  int32_t *row_token;                                    // [n_seg, max_rows]: token of each row, for runs too long for LDS
+  int32_t n_blocks, bin_stride, max_kc, max_rows;
 };
 
-__global__ __launch_bounds__(kBuildBlock) void build_rank_kernel(BuildArgs a) {
-  extern __shared__ uint32_t s_count[];  // two 16-bit counts per word: clusters 2 w and 2 w + 1 (a count is <= 1024)
-  __shared__ int s_id[kBuildBlock];      // ids of the tokens that share their cluster inside the block, in token order
-  __shared__ int s_scr[kBuildBlock / 64 + 1];
-  const int seg = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
+// LDS of one wave, read by lanes other than the writer: the wave's LDS operations execute in order, the compiler must
+// keep them in order too.
+__device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
+__device__ __forceinline__ uint64_t lanes_below() { return (1ull << lane_id()) - 1; }
+
+__global__ __launch_bounds__(kRankThreads) void build_rank_kernel(BuildArgs a) {
+  extern __shared__ uint32_t s_words[];  // 16-bit counts [kRankWaves][bin_stride]
+  uint16_t *const tab = reinterpret_cast<uint16_t *>(s_words);
+  const int seg = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x, wave = wave_id();
   const int n = min(a.seg_rows[seg], a.max_rows);
   if (blk * kBuildBlock >= n) return;
   const int c0 = a.seg_cluster_ptr[seg], kc = min(a.seg_cluster_ptr[seg + 1] - c0, a.max_kc);
-  const int t = blk * kBuildBlock + tid;
-  for (int w = tid; 2 * w < kc; w += kBuildBlock) s_count[w] = 0;
-  int c = -1;
-  if (t < n) {
-    c = a.assignment[a.seg_row_base[seg] + t];
-    if ((unsigned)c >= (unsigned)kc) c = -1;  // a token without a valid cluster is left out
-  }
-  __syncthreads();
-  if (c >= 0) atomicAdd(&s_count[c >> 1], 1u << (16 * (c & 1)));  // integer counts: any order gives the same table
-  __syncthreads();
-  int32_t *row = a.hist + ((size_t)seg * a.n_blocks + blk) * a.max_kc;
-  for (int i = tid; i < kc; i += kBuildBlock) row[i] = (int32_t)((s_count[i >> 1] >> (16 * (i & 1))) & 0xffffu);
-  const bool shared_id = c >= 0 && ((s_count[c >> 1] >> (16 * (c & 1))) & 0xffffu) > 1u;
-  int m;
-  const int pos = block_excl_scan<int, kBuildBlock / 64>(shared_id ? 1 : 0, s_scr, m);
-  if (shared_id) s_id[pos] = c;
-  __syncthreads();
-  if (c < 0) return;
-  int earlier = 0;
-  if (shared_id)  // the list is in token order: the earlier tokens are its first pos entries
-    for (int j = 0; j < pos; ++j) earlier += s_id[j] == c;
-  a.rank[((size_t)seg * a.n_blocks + blk) * kBuildBlock + tid] = (uint16_t)earlier;
-}
-
-__global__ __launch_bounds__(256) void build_scan_kernel(BuildArgs a) {
-  const int seg = blockIdx.y;
-  const int c0 = a.seg_cluster_ptr[seg], kc = min(a.seg_cluster_ptr[seg + 1] - c0, a.max_kc);
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= kc) return;
-  const int n = min(a.seg_rows[seg], a.max_rows);
-  const int blocks = (n + kBuildBlock - 1) / kBuildBlock;
-  int32_t *h = a.hist + (size_t)seg * a.n_blocks * a.max_kc + c;
-  int run = 0;
-  for (int b0 = 0; b0 < blocks; b0 += 8) {  // 8 independent loads in flight, then the running prefix
-    int v[8];
+  const int n_bins = (kc + kBinClusters - 1) / kBinClusters;
+  const int64_t r0 = a.seg_row_base[seg];
+  const int t0 = blk * kBuildBlock + wave * (64 * kRankRounds) + lane_id();  // a wave owns consecutive tokens
+  int c[kRankRounds];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = (b0 + u < blocks) ? h[(size_t)(b0 + u) * a.max_kc] : 0;
+  for (int u = 0; u < kRankRounds; ++u) c[u] = a.assignment[r0 + min(t0 + 64 * u, n - 1)];
+  for (int i = tid; i < kRankWaves * a.bin_stride / 2; i += kRankThreads) s_words[i] = 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (b0 + u < blocks) h[(size_t)(b0 + u) * a.max_kc] = run;
-      run += v[u];
+  for (int u = 0; u < kRankRounds; ++u) {
+    const int t = t0 + 64 * u;
+    if (t >= n || (unsigned)c[u] >= (unsigned)kc) {  // a token without a valid cluster is left out
+      c[u] = -1;
+      if (a.token_row && t < n) a.token_row[r0 + t] = -1;
     }
   }
-  a.cluster_sizes[c0 + c] = run;
+  __syncthreads();
+  uint16_t *const mine = tab + wave * a.bin_stride;
+  const int bits = n_bins > 1 ? 32 - __clz(n_bins - 1) : 0;
+  int rank[kRankRounds];
+#pragma unroll
+  for (int u = 0; u < kRankRounds; ++u) {
+    const int bin = c[u] >> 4;
+    const bool live = c[u] >= 0;
+    uint64_t peers = __ballot(live);
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = (bin >> b) & 1;
+      const uint64_t ones = __ballot(bit);
+      peers &= bit ? ones : ~ones;
+    }
+    const int before = live ? mine[bin] : 0;
+    const int ahead = __popcll(peers & lanes_below());
+    rank[u] = before + ahead;
+    wave_lds_order();
+    if (live && ahead == 0) mine[bin] = (uint16_t)(before + __popcll(peers));
+    wave_lds_order();
+  }
+  __syncthreads();
+  // per bin: exclusive prefix over the waves, in place; the block's count
+  int32_t *row = a.hist + ((size_t)seg * a.n_blocks + blk) * a.bin_stride;
+  for (int i = tid; i < n_bins; i += kRankThreads) {
+    int run = 0;
+#pragma unroll
+    for (int w = 0; w < kRankWaves; ++w) {
+      const int v = tab[w * a.bin_stride + i];
+      tab[w * a.bin_stride + i] = (uint16_t)run;
+      run += v;
+    }
+    row[i] = run;
+  }
+  __syncthreads();
+  uint16_t *out = a.rank + ((size_t)seg * a.n_blocks + blk) * kBuildBlock + wave * (64 * kRankRounds) + lane_id();
+#pragma unroll
+  for (int u = 0; u < kRankRounds; ++u)
+    if (c[u] >= 0) out[64 * u] = (uint16_t)(mine[c[u] >> 4] + rank[u]);
 }
 
-__global__ __launch_bounds__(1024) void build_offsets_kernel(BuildArgs a) {
+__global__ __launch_bounds__(1024) void build_scan_kernel(BuildArgs a) {
   __shared__ int scr[1024 / 64 + 1];
   const int seg = blockIdx.x, tid = threadIdx.x;
-  const int c0 = a.seg_cluster_ptr[seg], kc = a.seg_cluster_ptr[seg + 1] - c0;
+  const int c0 = a.seg_cluster_ptr[seg], kc_all = a.seg_cluster_ptr[seg + 1] - c0, kc = min(kc_all, a.max_kc);
+  const int n_bins = (kc + kBinClusters - 1) / kBinClusters;
+  const int n = min(a.seg_rows[seg], a.max_rows);
+  const int blocks = (n + kBuildBlock - 1) / kBuildBlock;
+  int32_t *start = a.bin_start + (size_t)seg * (a.bin_stride + 1);
   int carry = 0;
-  for (int i0 = 0; i0 < kc; i0 += 1024) {
+  for (int i0 = 0; i0 < n_bins; i0 += 1024) {
     const int i = i0 + tid;
-    // clusters beyond the host's bound received no size: they are reported empty
-    const int s = (i < kc && i < a.max_kc) ? a.cluster_sizes[c0 + i] : 0;
-    int tot;
-    const int ex = block_excl_scan<int, 1024 / 64>(s, scr, tot);
-    if (i < kc) {
-      a.cluster_offsets[c0 + i] = carry + ex;
-      if (i >= a.max_kc) a.cluster_sizes[c0 + i] = 0;
+    int run = 0;
+    if (i < n_bins) {
+      int32_t *h = a.hist + (size_t)seg * a.n_blocks * a.bin_stride + i;
+      constexpr int kBatch = 16;  // independent loads in flight, then the running prefix
+      for (int b0 = 0; b0 < blocks; b0 += kBatch) {
+        int v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) v[u] = h[(size_t)min(b0 + u, blocks - 1) * a.bin_stride];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+          if (b0 + u < blocks) {
+            h[(size_t)(b0 + u) * a.bin_stride] = run;
+            run += v[u];
+          }
+      }
     }
+    int tot;
+    const int ex = block_excl_scan<int, 1024 / 64>(run, scr, tot);
+    if (i < n_bins) start[i] = carry + ex;
     carry += tot;
+  }
+  if (tid == 0) start[n_bins] = carry;
+  // clusters beyond the host's bound received no token: they are reported empty
+  for (int i = a.max_kc + tid; i < kc_all; i += 1024) {
+    if (a.cluster_offsets) a.cluster_offsets[c0 + i] = carry;
+    if (a.cluster_sizes) a.cluster_sizes[c0 + i] = 0;
   }
 }
 
@@ -127,16 +173,13 @@ __global__ __launch_bounds__(256) void build_place_kernel(BuildArgs a) {
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= n) return;
   const int c0 = a.seg_cluster_ptr[seg], kc = min(a.seg_cluster_ptr[seg + 1] - c0, a.max_kc);
-  const int64_t r0 = a.seg_row_base[seg];
-  const int blk = t / kBuildBlock;
-  const int c = a.assignment[r0 + t];
-  int dest = -1;
-  if ((unsigned)c < (unsigned)kc) {
-    dest = a.cluster_offsets[c0 + c] + a.hist[((size_t)seg * a.n_blocks + blk) * a.max_kc + c] +
-           a.rank[(size_t)seg * a.n_blocks * kBuildBlock + t];
-    a.row_token[(size_t)seg * a.max_rows + dest] = t;
-  }
-  if (a.token_row) a.token_row[r0 + t] = dest;
+  const int c = a.assignment[a.seg_row_base[seg] + t];
+  const int rank = a.rank[(size_t)seg * a.n_blocks * kBuildBlock + t];  // (undefined for a token that is left out)
+  if ((unsigned)c >= (unsigned)kc) return;
+  const int bin = c / kBinClusters;
+  const int at = a.bin_start[(size_t)seg * (a.bin_stride + 1) + bin] +
+                 a.hist[((size_t)seg * a.n_blocks + t / kBuildBlock) * a.bin_stride + bin] + rank;
+  a.binned[(size_t)seg * a.max_rows + at] = (uint64_t)t * kBinClusters + (uint64_t)(c % kBinClusters);
 }
 
 // double -> bf16 bits with ONE rounding to 8 significant bits, ties to even.  Values whose magnitude
@@ -153,66 +196,151 @@ __device__ __forceinline__ uint32_t f64_to_bf16_rne(double x) {
   return bits;
 }
 
-// The move.  A workgroup owns 16 consecutive clusters, whose rows are one contiguous run of the cache.  The run is
-// taken in chunks of 64 rows: the sixteen 16-lane rows of the workgroup fetch four rows each (whatever the sizes
-// of the clusters, every lane has the same number of loads in flight), store them in place and leave a copy in LDS;
-// then thread d sums column d (key dimensions, then value dimensions) of the chunk's rows in row order, in fp64, and
-// writes a cluster's means when its last row has gone by.  A sum carries over from chunk to chunk.
-// kMove = false: keys only (the update step of k-means): nothing is stored in place, no value is read, and a cluster
-// without tokens keeps the centroid it has.
+// The move.  A workgroup owns a bin of 16 consecutive clusters, whose rows are one contiguous run of the cache.  It
+// first orders the bin's tokens by cluster (stable: a wave takes a consecutive share of the bin's list, 64 tokens at a
+// time; lane i < 16 counts cluster i); the list stays in LDS, or in global memory when the run is too long for that.
+// The run is then taken in chunks of 64 rows: the sixteen 16-lane rows of the workgroup fetch four rows each (whatever
+// the sizes of the clusters, every lane has the same number of loads in flight), leave a copy in LDS and store them in
+// place; the next chunk's rows are fetched while the chunk is summed.  Thread d sums column d (key dimensions, then
+// value dimensions) of the chunk's rows in row order, in fp64, and writes a cluster's means when its last row has gone
+// by.  A sum carries over from chunk to chunk.
+// kMove = false: keys only (the update step of k-means): nothing is stored in place, no value is read, the two halves
+// of the workgroup take the clusters in turn, and a cluster without tokens keeps the centroid it has.
 constexpr int kMoveRows = 64;
+constexpr int kListRows = 1024;  // longest run whose list stays in LDS
 
 template <bool kMove>
 __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
-  __shared__ __align__(16) uint16_t s_rows[kMoveRows][2 * kHeadDim];  // key | value of every row of the chunk
-  const int seg = blockIdx.y, tid = threadIdx.x;
-  const int c0 = a.seg_cluster_ptr[seg], kc = a.seg_cluster_ptr[seg + 1] - c0;
+  constexpr int kCols = kMove ? 2 * kHeadDim : kHeadDim;
+  __shared__ __align__(16) uint16_t s_rows[kMoveRows][kCols];  // key | value of every row of the chunk
+  __shared__ int s_list[kListRows];
+  __shared__ int s_cnt[4][kBinClusters];
+  const int seg = blockIdx.y, bin = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const int c0 = a.seg_cluster_ptr[seg], kc = min(a.seg_cluster_ptr[seg + 1] - c0, a.max_kc);
   const int64_t r0 = a.seg_row_base[seg];
-  const int cf = blockIdx.x * 16;
+  const int cf = bin * kBinClusters;
   if (cf >= kc) return;
-  const int ncl = min(16, kc - cf);
+  const int ncl = min(kBinClusters, kc - cf);
   const int lane16 = tid & 15, grp = tid >> 4;
-  // every 16-lane row holds the bounds of the workgroup's clusters, one per lane
-  const int cme = c0 + cf + min(lane16, ncl - 1);
-  const int sz = a.cluster_sizes[cme], off = a.cluster_offsets[cme];
-  const int run0 = __shfl(off, 0, 16), n_run = __shfl(off + sz, ncl - 1, 16) - run0;
-  const int my_end = off + sz - run0;  // where the cluster ends inside the run
+  const int32_t *start = a.bin_start + (size_t)seg * (a.bin_stride + 1) + bin;
+  const int run0 = start[0], n_run = start[1] - run0;
+  const uint64_t *binned = a.binned + (size_t)seg * a.max_rows + run0;
+  int32_t *far_list = a.row_token + (size_t)seg * a.max_rows + run0;
+  const bool in_lds = n_run <= kListRows;
 
-  const int32_t *tok = a.row_token + (size_t)seg * a.max_rows + run0;
-  // lanes u, u + 4, ... of a 16-lane row: the token of the row's u-th share of the chunk (row 16 u + grp)
-  auto token_of = [&](int base) { return tok[min(base + 16 * (lane16 & 3) + grp, n_run - 1)]; };
+  // ---- order the bin's tokens by cluster ----
+  const int share = 64 * ((n_run + 255) / 256), j0 = wave * share, j1 = min(n_run, j0 + share);
+  // the lanes of the wave that hold a token of cluster v, from the ballots of the id's four bits
+  struct Ballots {
+    uint64_t live, bit[4];
+    __device__ __forceinline__ uint64_t of(int v) const {
+      uint64_t m = live;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) m &= ((v >> b) & 1) ? bit[b] : ~bit[b];
+      return m;
+    }
+  };
+  auto ballots = [&](uint64_t word, bool live) {
+    Ballots s;
+    s.live = __ballot(live);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) s.bit[b] = __ballot((word >> b) & 1);
+    return s;
+  };
+  constexpr int kKeep = 2;  // list entries per lane that stay in registers from the first pass to the second
+  uint64_t kept[kKeep];
+  int count = 0;
+#pragma unroll
+  for (int u = 0; u < kKeep; ++u) {
+    const int j = j0 + 64 * u + lane;
+    kept[u] = n_run > 0 ? binned[min(j, n_run - 1)] : 0;
+  }
+  auto word_of = [&](int u) {
+    uint64_t w = 0;
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k)
+      if (u == k) w = kept[k];
+    if (u >= kKeep) w = binned[min(j0 + 64 * u + lane, n_run - 1)];
+    return w;
+  };
+  for (int u = 0; j0 + 64 * u < j1; ++u) {
+    const Ballots s = ballots(word_of(u), j0 + 64 * u + lane < j1);
+    count += __popcll(s.of(lane16));
+  }
+  if (lane < kBinClusters) s_cnt[wave][lane] = count;
+  __syncthreads();
+  int sz = 0, before = 0;  // of cluster lane16, in every 16-lane row: its size; its tokens in earlier waves' shares
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const int v = s_cnt[w][lane16];
+    sz += v;
+    before += w < wave ? v : 0;
+  }
+  const int my_end = row16_incl_scan(sz), my_off = my_end - sz;  // where the cluster lies inside the run
+  int next = my_off + before;
+  for (int u = 0; j0 + 64 * u < j1; ++u) {
+    const uint64_t word = word_of(u);
+    const bool live = j0 + 64 * u + lane < j1;
+    const Ballots s = ballots(word, live);
+    const int v = (int)(word & (kBinClusters - 1)), t = (int)(word / kBinClusters);
+    const int dest = __shfl(next, v, 16) + __popcll(s.of(v) & lanes_below());
+    next += __popcll(s.of(lane16));
+    if (live) {
+      if (in_lds) s_list[dest] = t;
+      else far_list[dest] = t;
+      if (a.token_row) a.token_row[r0 + t] = run0 + dest;
+    }
+  }
+  if (tid < ncl) {
+    if (a.cluster_offsets) a.cluster_offsets[c0 + cf + tid] = run0 + my_off;
+    if (a.cluster_sizes) a.cluster_sizes[c0 + cf + tid] = sz;
+  }
+  if (in_lds) lds_barrier();
+  else __syncthreads();  // (waits for the list's stores)
+
+  // ---- fetch, store in place, sum ----
+  uint4 kr[4], vr[4];
+  auto fetch = [&](int base) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // shares beyond the run fetch its last row again and are not stored
+      const int j = min(base + 16 * u + grp, n_run - 1);
+      const int t = in_lds ? s_list[j] : far_list[j];
+      kr[u] = load_row_slice(a.k_tokens, r0 + t, lane16);
+      if (kMove) vr[u] = load_row_slice(a.v_tokens, r0 + t, lane16);
+    }
+  };
   auto flush = [&](int c, int s, double sum) {
-    if (!kMove && (s == 0 || tid >= kHeadDim)) return;
+    if (!kMove && s == 0) return;
     const uint32_t bits = s > 0 ? f64_to_bf16_rne(sum / (double)s) : 0u;
     const size_t o = (size_t)(c0 + cf + c) * kHeadDim;
-    if (tid < kHeadDim) {
+    if (!kMove) {
+      static_cast<uint16_t *>(a.k_centroids)[o + (tid & (kHeadDim - 1))] = (uint16_t)bits;
+    } else if (tid < kHeadDim) {
       static_cast<uint16_t *>(a.k_centroids)[o + tid] = (uint16_t)bits;
     } else {
       static_cast<uint16_t *>(a.v_centroids)[o + tid - kHeadDim] = (uint16_t)bits;
       if (a.v_sums) a.v_sums[o + tid - kHeadDim] = (float)sum;
     }
   };
-
+  const int col = kMove ? tid : tid & (kHeadDim - 1);
+  constexpr int kStep = kMove ? 1 : 2;
   double acc = 0.0;
-  int cur = 0;  // the cluster whose rows are being summed: the same in every thread
-  int cur_end = __builtin_amdgcn_readfirstlane(__shfl(my_end, 0, 16));
-  int cur_sz = __builtin_amdgcn_readfirstlane(__shfl(sz, 0, 16));
-  int mine = n_run > 0 ? token_of(0) : 0;
+  // the cluster whose rows are being summed: the same in every thread (of a half)
+  int cur = kMove ? 0 : __builtin_amdgcn_readfirstlane(tid / kHeadDim);
+  int cur_off, cur_end;
+  auto bounds = [&]() {
+    cur_off = __builtin_amdgcn_readfirstlane(__shfl(my_off, cur & 15, 16));
+    cur_end = __builtin_amdgcn_readfirstlane(__shfl(my_end, cur & 15, 16));
+  };
+  bounds();
+  if (n_run > 0) fetch(0);
   for (int base = 0; base < n_run; base += kMoveRows) {
     const int nb = min(kMoveRows, n_run - base);
-    uint4 kr[4], vr[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {  // shares beyond the run fetch its last row again and are not stored
-      const int t = __shfl(mine, u, 16);
-      kr[u] = load_row_slice(a.k_tokens, r0 + t, lane16);
-      if (kMove) vr[u] = load_row_slice(a.v_tokens, r0 + t, lane16);
-    }
-    mine = token_of(base + kMoveRows);  // the next chunk's tokens arrive while this chunk is summed
-    lds_barrier();                      // the previous chunk has been summed
+    lds_barrier();  // the previous chunk has been summed
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       *reinterpret_cast<uint4 *>(&s_rows[16 * u + grp][lane16 * 8]) = kr[u];
-      if (kMove) *reinterpret_cast<uint4 *>(&s_rows[16 * u + grp][kHeadDim + lane16 * 8]) = vr[u];
+      if (kMove) *reinterpret_cast<uint4 *>(&s_rows[16 * u + grp][kCols - kHeadDim + lane16 * 8]) = vr[u];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {  // after the copies: a wait placed behind a store would wait for the store
@@ -223,49 +351,56 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
         *reinterpret_cast<uint4 *>(static_cast<char *>(a.v_cache) + row * kRowBytes + lane16 * 16) = vr[u];
       }
     }
+    if (base + kMoveRows < n_run) fetch(base + kMoveRows);  // in flight while this chunk is summed
     lds_barrier();
-    int j = 0;
     while (cur < ncl) {
+      int j = max(cur_off - base, 0);
       const int hi = min(cur_end - base, nb);
-      if (!kMove && tid >= kHeadDim) j = hi;  // keys only: the upper half of the workgroup has no column
       for (; j + 8 <= hi; j += 8) {
         uint16_t x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = s_rows[j + u][tid];
+        for (int u = 0; u < 8; ++u) x[u] = s_rows[j + u][col];
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc += (double)__uint_as_float((uint32_t)x[u] << 16);
       }
-      for (; j < hi; ++j) acc += (double)__uint_as_float((uint32_t)s_rows[j][tid] << 16);
+      for (; j < hi; ++j) acc += (double)__uint_as_float((uint32_t)s_rows[j][col] << 16);
       if (cur_end - base > nb) break;  // the cluster goes on in the next chunk
-      flush(cur, cur_sz, acc);
+      flush(cur, cur_end - cur_off, acc);
       acc = 0.0;
-      ++cur;
-      if (cur < ncl) {
-        cur_end = __builtin_amdgcn_readfirstlane(__shfl(my_end, cur, 16));
-        cur_sz = __builtin_amdgcn_readfirstlane(__shfl(sz, cur, 16));
-      }
+      cur += kStep;
+      bounds();
     }
   }
-  for (; cur < ncl; ++cur)  // a workgroup without rows: its clusters are empty
+  for (; cur < ncl; cur += kStep)  // a workgroup without rows: its clusters are empty
     flush(cur, 0, 0.0);
+}
+
+struct BuildLayout {
+  size_t hist, rank, bin_start, binned, row_token, total;  // byte offsets
+  int n_blocks, bin_stride;
+};
+BuildLayout layout_of(int n_seg, int max_rows, int max_kc) {
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  BuildLayout L;
+  L.n_blocks = (int)(((int64_t)max_rows + kBuildBlock - 1) / kBuildBlock);
+  L.bin_stride = ((max_kc + kBinClusters - 1) / kBinClusters + 1) / 2 * 2;  // even: the tables are cleared word by word
+  L.hist = 0;
+  L.rank = up((size_t)n_seg * L.n_blocks * L.bin_stride * sizeof(int32_t));
+  L.bin_start = L.rank + up((size_t)n_seg * L.n_blocks * kBuildBlock * sizeof(uint16_t));
+  L.binned = L.bin_start + up((size_t)n_seg * (L.bin_stride + 1) * sizeof(int32_t));
+  L.row_token = L.binned + up((size_t)n_seg * max_rows * sizeof(uint64_t));
+  L.total = L.row_token + up((size_t)n_seg * max_rows * sizeof(int32_t));
+  return L;
 }
 
 }  // namespace
 
-void build_workspace_layout(int n_seg, int max_rows, int max_kc, size_t *hist_bytes, size_t *rank_bytes,
-                            size_t *row_token_bytes, int *n_blocks) {
-  const int nb = (max_rows + kBuildBlock - 1) / kBuildBlock;
-  *n_blocks = nb;
-  *hist_bytes = ((size_t)n_seg * nb * max_kc * sizeof(int32_t) + 255) / 256 * 256;
-  *rank_bytes = ((size_t)n_seg * nb * kBuildBlock * sizeof(uint16_t) + 255) / 256 * 256;
-  *row_token_bytes = ((size_t)n_seg * max_rows * sizeof(int32_t) + 255) / 256 * 256;
-}
+size_t build_workspace_bytes(int n_seg, int max_rows, int max_kc) { return layout_of(n_seg, max_rows, max_kc).total; }
 
 hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s) {
   if (p.n_seg == 0) return hipSuccess;
-  size_t hist_bytes, rank_bytes, row_token_bytes;
-  int n_blocks;
-  build_workspace_layout(p.n_seg, p.max_rows, p.max_kc, &hist_bytes, &rank_bytes, &row_token_bytes, &n_blocks);
+  const BuildLayout L = layout_of(p.n_seg, p.max_rows, p.max_kc);
+  char *ws = static_cast<char *>(workspace);
   BuildArgs a;
   a.k_tokens = p.k_tokens;
   a.v_tokens = p.v_tokens;
@@ -281,29 +416,30 @@ hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s) {
   a.cluster_sizes = p.cluster_sizes;
   a.token_row = p.token_row;
   a.v_sums = p.v_sums;
-  a.hist = static_cast<int32_t *>(workspace);
-  a.rank = reinterpret_cast<uint16_t *>(static_cast<char *>(workspace) + hist_bytes);
-  a.row_token = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + hist_bytes + rank_bytes);
-  a.n_blocks = n_blocks;
+  a.hist = reinterpret_cast<int32_t *>(ws + L.hist);
+  a.rank = reinterpret_cast<uint16_t *>(ws + L.rank);
+  a.bin_start = reinterpret_cast<int32_t *>(ws + L.bin_start);
+  a.binned = reinterpret_cast<uint64_t *>(ws + L.binned);
+  a.row_token = reinterpret_cast<int32_t *>(ws + L.row_token);
+  a.n_blocks = L.n_blocks;
+  a.bin_stride = L.bin_stride;
   a.max_kc = p.max_kc;
   a.max_rows = p.max_rows;
-  if (n_blocks > 0 && p.max_kc > 0) {
-    // the count table of a block lives in LDS: 2 bytes per cluster of the longest segment (128 KB at the 65536 limit)
-    const size_t lds = ((size_t)p.max_kc + 1) / 2 * sizeof(uint32_t);
+  if (L.n_blocks > 0 && L.bin_stride > 0) {
+    // a count per wave and bin lives in LDS: 2 bytes per cluster of the longest segment (128 KB at the 65536 limit)
+    const size_t lds = (size_t)kRankWaves * L.bin_stride * sizeof(uint16_t);
     if (lds > 32768) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(build_rank_kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(build_rank_kernel, dim3(n_blocks, p.n_seg), dim3(kBuildBlock), lds, s, a);
+    hipLaunchKernelGGL(build_rank_kernel, dim3(L.n_blocks, p.n_seg), dim3(kRankThreads), lds, s, a);
   }
-  if (p.max_kc > 0)
-    hipLaunchKernelGGL(build_scan_kernel, dim3((p.max_kc + 255) / 256, p.n_seg), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(build_offsets_kernel, dim3(p.n_seg), dim3(1024), 0, s, a);
-  if (n_blocks > 0 && p.max_kc > 0)
+  hipLaunchKernelGGL(build_scan_kernel, dim3(p.n_seg), dim3(1024), 0, s, a);
+  if (L.n_blocks > 0 && p.max_kc > 0)
     hipLaunchKernelGGL(build_place_kernel, dim3((p.max_rows + 255) / 256, p.n_seg), dim3(256), 0, s, a);
   if (p.max_kc > 0) {
-    const dim3 grid((p.max_kc + 15) / 16, p.n_seg);
+    const dim3 grid((p.max_kc + kBinClusters - 1) / kBinClusters, p.n_seg);
     if (p.k_cache) hipLaunchKernelGGL(build_move_kernel<true>, grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(build_move_kernel<false>, grid, dim3(256), 0, s, a);
   }

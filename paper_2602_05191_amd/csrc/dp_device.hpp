@@ -198,11 +198,15 @@ __device__ __forceinline__ float wave_max(float v) {
 
 // Inclusive wave scans of integers: a shift-and-add scan inside each 16-lane row with DPP row shifts (a lane
 // without a source reads 0), then the totals of the rows before (lanes 15, 31, 47, through readlane) are added.
-__device__ __forceinline__ int wave_incl_scan(int v) {
+__device__ __forceinline__ int row16_incl_scan(int v) {
   v += (int)dpp_mov_u32<0x111>((uint32_t)v);  // row_shr:1
   v += (int)dpp_mov_u32<0x112>((uint32_t)v);  // row_shr:2
   v += (int)dpp_mov_u32<0x114>((uint32_t)v);  // row_shr:4
   v += (int)dpp_mov_u32<0x118>((uint32_t)v);  // row_shr:8
+  return v;
+}
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v = row16_incl_scan(v);
   const int t0 = (int)lane_u32((uint32_t)v, 15), t1 = (int)lane_u32((uint32_t)v, 31), t2 = (int)lane_u32((uint32_t)v, 47);
   const int row = lane_id() >> 4;
   return v + (row == 0 ? 0 : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);

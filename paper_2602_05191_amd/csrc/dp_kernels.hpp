@@ -136,11 +136,10 @@ struct BuildProblem {
   const int32_t *seg_rows, *seg_cluster_ptr;
   int32_t max_kc, max_rows;
   void *k_cache, *v_cache, *k_centroids, *v_centroids;
-  int32_t *cluster_offsets, *cluster_sizes, *token_row;  // token_row nullable
+  int32_t *cluster_offsets, *cluster_sizes, *token_row;  // all nullable
   float *v_sums;                                         // nullable
 };
-void build_workspace_layout(int n_seg, int max_rows, int max_kc, size_t *hist_bytes, size_t *rank_bytes,
-                            size_t *row_token_bytes, int *n_blocks);
+size_t build_workspace_bytes(int n_seg, int max_rows, int max_kc);
 hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s);
 
 // k-means assignment step: nearest centroid of every token (dp_kmeans.hip)

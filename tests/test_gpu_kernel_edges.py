@@ -37,3 +37,49 @@ def test_dense_decode_deals_rows_out_over_ragged_segments():
     # as above; 4000 rows
     assert np.abs(out - ref)[~empty].max() <= 2e-5
     assert np.abs(lse - ref_lse)[~empty].max() <= 2e-5 * np.abs(ref_lse).max()
+
+
+def _tokens(rows, clusters, spread, seed):
+    """Token-order K / V with ids drawn as ``spread`` says."""
+    from workloads import TokenOrderInput
+    rng = np.random.default_rng(seed)
+    ids = []
+    for n, kc in zip(rows, clusters):
+        if spread == "uniform":
+            a = rng.integers(0, kc, size=n)
+        elif spread == "one_bin":       # (nearly) everything in the last 16 clusters: one long run
+            a = np.where(rng.random(n) < 0.98, kc - 1 - rng.integers(0, min(kc, 16), size=n), rng.integers(0, kc, size=n))
+        else:                           # runs of equal ids, some of them invalid
+            a = np.repeat(rng.integers(-1, kc + 1, size=n // 50 + 1), 50)[:n]
+        ids.append(a)
+    rows = np.asarray(rows, np.int32)
+    bits = rng.integers(0, 1 << 16, size=(2, int(rows.sum()), 128), dtype=np.uint16)
+    bits = (bits & 0x807F) | np.uint16(0x3F80) - (bits & 0x0300)   # finite values of a few exponents, both signs
+    return TokenOrderInput(n_seg=len(rows), head_dim=128, k_tokens=bits[0].copy(), v_tokens=bits[1].copy(),
+                           assignment=np.concatenate(ids).astype(np.int32),
+                           seg_row_base=np.concatenate([[0], np.cumsum(rows)[:-1]]).astype(np.int64), seg_rows=rows,
+                           seg_cluster_ptr=np.concatenate([[0], np.cumsum(clusters)]).astype(np.int32))
+
+
+@pytest.mark.parametrize("spread", ["uniform", "one_bin", "runs"])
+@pytest.mark.parametrize("clusters", [1, 16, 17, 33, 1000])
+def test_build_at_block_bin_and_list_edges(clusters, spread):
+    """Token blocks of 4096, waves of 64, bins of 16 clusters, runs above and below the 1024 tokens whose list stays in
+    LDS, chunks of 64 rows.  Bit-exact, as in test_gpu_build."""
+    from test_gpu_build import check_build, gpu_build
+    rows = [1, 63, 65, 1023, 1025, 4095, 4096, 4097, 9000]
+    t = _tokens(rows, [clusters] * len(rows), spread, seed=70 + clusters)
+    check_build(t, gpu_build(t), oracle.build_cluster_cache(t))
+
+
+@pytest.mark.parametrize("clusters", [2, 17])
+def test_kmeans_update_on_long_clusters(clusters):
+    """The keys-only move (two halves of a workgroup take the clusters in turn) over runs of 64 to 9000 rows: after
+    one round from given, well separated centroids the new centroids are the oracle's bits."""
+    import paper_2602_05191_amd as dp
+    from test_gpu_kmeans import gpu_fit, grouped_keys
+    rows = [64, 65, 1500, 9000]
+    t = grouped_keys(83, rows=rows, clusters=[clusters] * len(rows), groups=clusters)
+    ref_c, ref_a = oracle.kmeans_fit(t, None, 1, oracle.KMEANS_INIT_STRIDED)
+    got_c, got_a, _ = gpu_fit(t, None, 1, dp.DP_KMEANS_INIT_STRIDED)
+    assert np.array_equal(got_a, ref_a) and np.array_equal(got_c, ref_c)
