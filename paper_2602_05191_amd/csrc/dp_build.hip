@@ -28,7 +28,7 @@
 // own per bin.  So the cost does not depend on how the ids are distributed.
 // (One level with a count per 1024-token block and cluster needed 33 MB of counts for
 // 8 x 131072 tokens and 8192 clusters, and compared tokens of equal id pairwise: 64 us in
-// four kernels in front of the move; the three kernels here take 27.)
+// four kernels in front of the move; the three kernels here take 25.)
 // The update step of k-means (mean key of every cluster, nothing moved) is the same
 // sequence with the cache pointers left null: the last kernel then fetches keys only and stores no row.
 #include "dp_device.hpp"
@@ -204,6 +204,8 @@ __device__ __forceinline__ uint32_t f64_to_bf16_rne(double x) {
 // place; the next chunk's rows are fetched while the chunk is summed.  Thread d sums column d (key dimensions, then
 // value dimensions) of the chunk's rows in row order, in fp64, and writes a cluster's means when its last row has gone
 // by.  A sum carries over from chunk to chunk.
+// Rows go by once: non-temporal loads and stores (move of 8 x 131072 tokens 228 -> 215 us = 5.2 TB/s over 1.11 GB; a
+// plain copy of 2 GB runs at 4.7 TB/s on the same card).
 // kMove = false: keys only (the update step of k-means): nothing is stored in place, no value is read, the two halves
 // of the workgroup take the clusters in turn, and a cluster without tokens keeps the centroid it has.
 constexpr int kMoveRows = 64;
@@ -299,14 +301,25 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   else __syncthreads();  // (waits for the list's stores)
 
   // ---- fetch, store in place, sum ----
-  uint4 kr[4], vr[4];
-  auto fetch = [&](int base) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 kr[4], vr[4];
+  auto fetch = [&](int base, u32x4 (&kr)[4], u32x4 (&vr)[4]) {
+    int t[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {  // shares beyond the run fetch its last row again and are not stored
-      const int j = min(base + 16 * u + grp, n_run - 1);
-      const int t = in_lds ? s_list[j] : far_list[j];
-      kr[u] = load_row_slice(a.k_tokens, r0 + t, lane16);
-      if (kMove) vr[u] = load_row_slice(a.v_tokens, r0 + t, lane16);
+    for (int u = 0; u < 4; ++u)  // shares beyond the run fetch its last row again and are not stored
+      t[u] = s_list[min(min(base + 16 * u + grp, n_run - 1), kListRows - 1)];
+    if (!in_lds) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = far_list[min(base + 16 * u + grp, n_run - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t at = (r0 + t[u]) * kRowBytes + lane16 * 16;
+      const u32x4 *k = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.k_tokens) + at);
+      // (the keys-only form reads rows that the next round reads again: plain loads, so that they may stay cached)
+      kr[u] = kMove ? __builtin_nontemporal_load(k) : *k;
+      if (kMove)
+        vr[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.v_tokens) + at));
     }
   };
   auto flush = [&](int c, int s, double sum) {
@@ -333,25 +346,27 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
     cur_end = __builtin_amdgcn_readfirstlane(__shfl(my_end, cur & 15, 16));
   };
   bounds();
-  if (n_run > 0) fetch(0);
+  if (n_run > 0) fetch(0, kr, vr);
   for (int base = 0; base < n_run; base += kMoveRows) {
     const int nb = min(kMoveRows, n_run - base);
     lds_barrier();  // the previous chunk has been summed
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      *reinterpret_cast<uint4 *>(&s_rows[16 * u + grp][lane16 * 8]) = kr[u];
-      if (kMove) *reinterpret_cast<uint4 *>(&s_rows[16 * u + grp][kCols - kHeadDim + lane16 * 8]) = vr[u];
+      *reinterpret_cast<u32x4 *>(&s_rows[16 * u + grp][lane16 * 8]) = kr[u];
+      if constexpr (kMove) *reinterpret_cast<u32x4 *>(&s_rows[16 * u + grp][kHeadDim + lane16 * 8]) = vr[u];
     }
+    if constexpr (kMove) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {  // after the copies: a wait placed behind a store would wait for the store
-      const int j = 16 * u + grp;
-      if (kMove && j < nb) {
-        const int64_t row = r0 + run0 + base + j;
-        *reinterpret_cast<uint4 *>(static_cast<char *>(a.k_cache) + row * kRowBytes + lane16 * 16) = kr[u];
-        *reinterpret_cast<uint4 *>(static_cast<char *>(a.v_cache) + row * kRowBytes + lane16 * 16) = vr[u];
+      for (int u = 0; u < 4; ++u) {  // after the copies: a wait placed behind a store would wait for the store
+        const int j = 16 * u + grp;
+        if (j < nb) {
+          const int64_t at = (r0 + run0 + base + j) * kRowBytes + lane16 * 16;
+          __builtin_nontemporal_store(kr[u], reinterpret_cast<u32x4 *>(static_cast<char *>(a.k_cache) + at));
+          __builtin_nontemporal_store(vr[u], reinterpret_cast<u32x4 *>(static_cast<char *>(a.v_cache) + at));
+        }
       }
     }
-    if (base + kMoveRows < n_run) fetch(base + kMoveRows);  // in flight while this chunk is summed
+    if (base + kMoveRows < n_run) fetch(base + kMoveRows, kr, vr);  // in flight while this chunk is summed
     lds_barrier();
     while (cur < ncl) {
       int j = max(cur_off - base, 0);
