@@ -83,3 +83,42 @@ def test_kmeans_update_on_long_clusters(clusters):
     ref_c, ref_a = oracle.kmeans_fit(t, None, 1, oracle.KMEANS_INIT_STRIDED)
     got_c, got_a, _ = gpu_fit(t, None, 1, dp.DP_KMEANS_INIT_STRIDED)
     assert np.array_equal(got_a, ref_a) and np.array_equal(got_c, ref_c)
+
+
+@pytest.mark.parametrize("last", [6010, 60])
+def test_kmeans_assign_same_bits_whatever_the_launch(last):
+    """Eight segments together take 128 tokens per wave (2048 centroids per segment on average) or 64 (fewer); one
+    alone takes 32.  The same products are summed in the same order: index and score are equal to the bit, at token
+    and centroid counts around the tiles, for equal centroids in one quad and far apart, and with NaN and inf."""
+    import torch
+    import paper_2602_05191_amd as dp
+    rows = [32769, 1, 127, 128, 129, 511, 513, 2049]
+    clusters = [4099, 2048, 1, 3, 0, 66, 4163, last]
+    g = torch.Generator().manual_seed(91)
+    keys = torch.randn(sum(rows), 128, generator=g).bfloat16()
+    cent = torch.randn(sum(clusters), 128, generator=g).bfloat16()
+    cent[[5, 6, 70, 4098]] = cent[4].clone()          # one quad and the next, another block, the last
+    cent[4099 + 17, 3], cent[4099 + 18, 4], cent[4099 + 40, 5] = float("nan"), float("inf"), float("-inf")
+    keys[100, 7], keys[101, 8] = float("nan"), float("inf")
+    keys, cent = keys.cuda(), cent.cuda()
+    base, ptr = np.concatenate([[0], np.cumsum(rows)]), np.concatenate([[0], np.cumsum(clusters)])
+
+    def assign(segs):
+        first, end = ptr[segs[0]], ptr[segs[-1] + 1]
+        dev = lambda a, dt: torch.from_numpy(np.asarray(a, dt)).cuda()
+        pf = dp.Prefill(keys, keys, torch.zeros(len(keys), dtype=torch.int32, device="cuda"), dev(base[segs], np.int64),
+                        dev([rows[s] for s in segs], np.int32), dev(ptr[segs[0]:segs[-1] + 2] - first, np.int32),
+                        int(end - first), max(clusters[s] for s in segs), max(rows[s] for s in segs))
+        ws = torch.empty(max(dp.dp_kmeans_workspace_bytes(pf), 256), dtype=torch.uint8, device="cuda")
+        asg = torch.full((len(keys),), -7, dtype=torch.int32, device="cuda")
+        score = torch.full((len(keys),), -7.0, device="cuda")
+        dp.dp_kmeans_assign(pf, cent[first:max(end, first + 1)].contiguous(), asg, ws, best_score=score)
+        torch.cuda.synchronize()
+        return asg, score
+
+    asg, score = assign(list(range(8)))
+    assert not torch.isin(asg[:rows[0]], torch.tensor([5, 6, 70, 4098], device="cuda")).any()
+    for s in range(8):
+        one, one_score = assign([s])
+        at = slice(int(base[s]), int(base[s + 1]))
+        assert torch.equal(asg[at], one[at]) and torch.equal(score[at], one_score[at]), f"segment {s}"
