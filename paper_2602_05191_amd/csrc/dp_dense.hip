@@ -21,6 +21,10 @@
 //           the operand of the n-th of eight output tiles.
 // The running maximum of a head is the same in the four lanes that hold it, so the
 // rescaling of the accumulators is lane-local; it is skipped while no maximum moves.
+// Values that are not finite stay where they belong: a row that is loaded in place of one past the range has its
+// value replaced by zero (an infinite value times the weight 0 would be NaN); a maximum of -inf (no row yet, or only
+// rows that score -inf) is taken as the lowest finite number when it is subtracted (-inf - -inf would be NaN); weights
+// keep the range below 2^-126 (exp2f, not the bare instruction, which flushes it: a value of 1e38 there still counts).
 // Matrix-core time per 16 rows: 4 x 16 + 32 x 32 cycles, whatever the group size is:
 // 29 us at 2.4 GHz for the million rows of 8 x 131072 tokens, behind 87 us of HBM
 // time at 6.2 TB/s.  Measured there at G = 4: 82 us = 6.5 TB/s with non-temporal
@@ -91,12 +95,16 @@ __device__ __forceinline__ DenseShare dense_share(const DenseArgs &a, int *s_sca
   return d;
 }
 
+// what is subtracted from a score whose running maximum is m
+__device__ __forceinline__ float finite_max(float m) { return fmaxf(m, -3.402823466e38f); }
+
 // one wave's 16 cache rows as the two contractions want them
 struct DenseTile {
   uint4 k[4], v[4];
 };
 
-// Rows beyond the range read its last row: a lane's loads never leave the segment, and their weight is zero.
+// Rows beyond the range read its last row: a lane's loads never leave the segment, and their weight and values are
+// made zero before they are used.
 // (row0 and t are uniform in the wave: the tile's base is a scalar, a lane adds a 32-bit offset.)
 __device__ __forceinline__ void load_dense_tile(const DenseArgs &a, int64_t row0, int t, int last, int r, int kq,
                                                 DenseTile &d) {
@@ -156,7 +164,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     for (int n = 0; n < 8; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;  // head r: the maximum of all rows so far, the weights of this lane's rows
 
-    auto attend = [&](const DenseTile &d, int t) {
+    auto attend = [&](DenseTile &d, int t) {
       f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -170,17 +178,23 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
       }
       top = fmaxf(top, xor16(top));
       top = fmaxf(top, xor32(top));
-      if (__ballot(top > m)) {  // finite from the first tile on: its first row is inside the range
-        const float alpha = __builtin_amdgcn_exp2f(m - top);
+      if (__ballot(top > m)) {
+        const float alpha = exp2f(m - finite_max(top));
         l *= alpha;
 #pragma unroll
         for (int n = 0; n < 8; ++n) acc[n] *= alpha;
         m = top;
       }
+      const float sub = finite_max(m);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        x[i] = __builtin_amdgcn_exp2f(x[i] - m);
+        x[i] = exp2f(x[i] - sub);
         l += x[i];
+      }
+      if (t + kDenseTile > rb) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (t + 4 * kq + i >= rb) d.v[i] = make_uint4(0, 0, 0, 0);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -233,7 +247,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
       for (int w = 0; w < kDenseWaves; ++w) M = fmaxf(M, s_m[w][j]);
 #pragma unroll
       for (int w = 0; w < kDenseWaves; ++w) {
-        const float wg = (s_m[w][j] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s_m[w][j] - M);
+        const float wg = (s_m[w][j] == -INFINITY) ? 0.f : exp2f(s_m[w][j] - M);
         L += s_l[w][j] * wg;
         o += s_acc[w][j][d] * wg;
       }
@@ -286,15 +300,18 @@ __global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(De
     float Mn = Mx;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (s0 + kMergeGroups * u >= n_active) ms[u] = -INFINITY;  // (a live split's m is finite)
+      if (s0 + kMergeGroups * u >= n_active) {
+        ms[u] = -INFINITY;
+        ll[u] = oo[u] = 0.f;
+      }
       Mn = fmaxf(Mn, ms[u]);
     }
-    const float sc = __builtin_amdgcn_exp2f(Mx - Mn);
+    const float sub = finite_max(Mn), sc = exp2f(Mx - sub);
     Ls *= sc;
     os *= sc;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const float w = __builtin_amdgcn_exp2f(ms[u] - Mn);
+      const float w = exp2f(ms[u] - sub);
       Ls = fmaf(ll[u], w, Ls);
       os = fmaf(oo[u], w, os);
     }
@@ -312,7 +329,7 @@ __global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(De
   for (int v = 1; v < kMergeGroups; ++v) M = fmaxf(M, s_m[v]);
 #pragma unroll
   for (int v = 0; v < kMergeGroups; ++v) {
-    const float w = __builtin_amdgcn_exp2f(s_m[v] - M);
+    const float w = exp2f(s_m[v] - finite_max(M));
     L = fmaf(s_l[v], w, L);
     o = fmaf(s_o[v][t], w, o);
   }

@@ -39,6 +39,53 @@ def test_dense_decode_deals_rows_out_over_ragged_segments():
     assert np.abs(lse - ref_lse)[~empty].max() <= 2e-5 * np.abs(ref_lse).max()
 
 
+BF16 = {"inf": 0x7F80, "-inf": 0xFF80, "one": 0x3F80, "huge": 0x7F62}   # huge = 3.004e38
+
+
+def _dense_against_oracle(c, rtol=2e-5):
+    """Equal non-finite elements, the others as above (relative to their size where that is above 1)."""
+    out, lse = H.gpu_dense_decode(c, H.segment_rows(c))
+    ref, ref_lse, _ = oracle.Oracle(c).dense_step(n_threads=4)
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(np.isinf(out), np.isinf(ref))
+    fin = np.isfinite(ref)
+    assert (np.abs(out[fin] - ref[fin]) <= rtol * np.maximum(np.abs(ref[fin]), 1.0)).all()
+    assert np.abs(lse - ref_lse).max() <= 2e-5 * np.maximum(np.abs(ref_lse).max(), 1.0)
+    return out
+
+
+@pytest.mark.parametrize("n", [1, 37, 48, 64, 100, 1000])
+def test_dense_decode_keeps_an_infinite_value_in_its_dimension(n):
+    """An infinity in the segment's last V row, at lengths that are and are not multiples of the tile of 16."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=4, context=n, mean_cluster=16, q_scale=0.3, seed=63)
+    c.v_cache[n - 1, 5] = BF16["inf"]
+    out = _dense_against_oracle(c)
+    assert np.isposinf(out[..., 5]).all() and np.isfinite(np.delete(out, 5, axis=-1)).all()
+
+
+@pytest.mark.parametrize("n, lo, hi", [(300, 64, 128), (300, 0, 16), (1000, 0, 900), (37, 32, 37)])
+def test_dense_decode_rows_that_score_minus_infinity_have_no_weight(n, lo, hi):
+    """Whole tiles and whole 64-row chunks whose every row scores -inf, in front of, between and behind the others."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=4, context=n, mean_cluster=16, q_scale=0.3, seed=64)
+    c.q[..., 7] = BF16["one"]
+    c.k_cache[lo:hi, 7] = BF16["-inf"]
+    assert np.isfinite(_dense_against_oracle(c)).all()
+
+
+@pytest.mark.parametrize("gap", [86, 90, 95])
+def test_dense_decode_weights_below_the_normal_range_count(gap):
+    """One row of weight e^-gap (below 2^-126 from 88 on) with values of 3e38: the product is of ordinary size."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=4, context=40, mean_cluster=16, q_scale=0.3, seed=65)
+    c.q[:], c.k_cache[:], c.v_cache[:] = 0, 0, 0
+    c.q[..., 0] = BF16["one"]
+    c.k_cache[1:, 0] = np.float32([-gap * 128 ** 0.5]).view(np.uint32)[0] >> 16
+    c.v_cache[1, 5] = BF16["huge"]
+    # the weight is a multiple of 2^-149, so it is off by up to 2^-150 / e^-gap of itself; the score (up to 137 in base
+    # 2) is rounded to 2^-17 at each of three steps, and that is what the weight is off by as well
+    bar = 2.0 ** -150 / np.exp(-gap) + 3 * 2.0 ** -17
+    out = _dense_against_oracle(c, rtol=bar)
+    assert (out[..., 5] > 0).all()
+
+
 def _tokens(rows, clusters, spread, seed):
     """Token-order K / V with ids drawn as ``spread`` says."""
     from workloads import TokenOrderInput
