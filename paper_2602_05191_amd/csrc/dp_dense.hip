@@ -19,6 +19,12 @@
 //           the output is read back alike: load instruction i fetches 16 B per lane
 //           (whole rows, dims 8 (l % 16) .. + 7), and its n-th value widened to fp32 is
 //           the operand of the n-th of eight output tiles.
+// Precision: scores are four products over 32 dimensions summed pairwise (4.7e-8 of their size against fp64; one chain
+// through the four instructions: 5.9e-8), scaled inside the subtraction of the maximum (one rounding less).  An fp32
+// matrix instruction adds its four rows one after the other, so a tile's 16 rows are summed by themselves and added to
+// the accumulator: its chain is as long as the wave has tiles, not rows (output against fp64, 131072 rows x 8 KV heads:
+// 4.1e-7 -> 1.7e-7 with flat weights, 1.0e-6 -> 5.0e-7 with scores of deviation 3; the vector-ALU form had 3.0e-7 and
+// 6.5e-7).
 // The running maximum of a head is the same in the four lanes that hold it, so the
 // rescaling of the accumulators is lane-local; it is skipped while no maximum moves.
 // Values that are not finite stay where they belong: a row that is loaded in place of one past the range has its
@@ -165,19 +171,19 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     float m = -INFINITY, l = 0.f;  // head r: the maximum of all rows so far, the weights of this lane's rows
 
     auto attend = [&](DenseTile &d, int t) {
-      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      f32x4 part[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, d.k[j]),
-                                                    __builtin_bit_cast(bf16x8, Q[j]), x, 0, 0, 0);
-      float top = m;
+        part[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, d.k[j]),
+                                                          __builtin_bit_cast(bf16x8, Q[j]), zero, 0, 0, 0);
+      f32x4 x = (part[0] + part[1]) + (part[2] + part[3]);  // unscaled
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        x[i] = t + 4 * kq + i < rb ? x[i] * a.scale_log2 : -INFINITY;
-        top = fmaxf(top, x[i]);
-      }
+      for (int i = 0; i < 4; ++i) x[i] = t + 4 * kq + i < rb ? x[i] : -INFINITY;
+      float top = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
       top = fmaxf(top, xor16(top));
       top = fmaxf(top, xor32(top));
+      top = fmaxf(m, top * a.scale_log2);
       if (__ballot(top > m)) {
         const float alpha = exp2f(m - finite_max(top));
         l *= alpha;
@@ -187,22 +193,24 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
       }
       const float sub = finite_max(m);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        x[i] = exp2f(x[i] - sub);
-        l += x[i];
-      }
+      for (int i = 0; i < 4; ++i) x[i] = exp2f(fmaf(x[i], a.scale_log2, -sub));
+      l += (x[0] + x[1]) + (x[2] + x[3]);
       if (t + kDenseTile > rb) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (t + 4 * kq + i >= rb) d.v[i] = make_uint4(0, 0, 0, 0);
       }
+      f32x4 sum[8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         float v[8];
         unpack8(d.v[i], v);
 #pragma unroll
-        for (int n = 0; n < 8; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[n], x[i], acc[n], 0, 0, 0);
+        for (int n = 0; n < 8; ++n)
+          sum[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[n], x[i], i == 0 ? zero : sum[n], 0, 0, 0);
       }
+#pragma unroll
+      for (int n = 0; n < 8; ++n) acc[n] += sum[n];
     };
 
     // the workgroup's waves take tiles in turn; the next tile's loads are in flight during a tile's arithmetic

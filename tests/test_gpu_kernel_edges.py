@@ -86,6 +86,21 @@ def test_dense_decode_weights_below_the_normal_range_count(gap):
     assert (out[..., 5] > 0).all()
 
 
+@pytest.mark.parametrize("seed", [66, 67])
+def test_dense_decode_long_sums_keep_fp32_precision(seed):
+    """One segment of 16384 rows among 128 (2048 heads: 8 partial slots each, so a wave sums 592 rows one after the
+    other) with weights of similar size and values of both signs."""
+    ctx = [16384] + [1] * 127
+    c = make_cache(batch=128, n_kv_heads=1, n_q_heads=16, context=ctx, mean_cluster=16, q_scale=0.05, seed=seed)
+    out, _ = H.gpu_dense_decode(c, H.segment_rows(c))
+    ref, _, _ = oracle.Oracle(c).dense_step(n_threads=4)
+    rel = np.linalg.norm(out[0] - ref[0]) / np.linalg.norm(ref[0])
+    # A chain of n fp32 sums of random sign is off by 2^-24 / sqrt(3) x sqrt(n / 2) of the result: 16 rows of a tile and
+    # 37 tiles give 1.8e-7, one chain over 592 rows 5.9e-7.  Scores of rms 3 (base 2), off by 6e-8 and rounded twice,
+    # add 2.5e-7: together 3.1e-7 against 6.4e-7.
+    assert rel <= 4.2e-7, rel
+
+
 def _tokens(rows, clusters, spread, seed):
     """Token-order K / V with ids drawn as ``spread`` says."""
     from workloads import TokenOrderInput
