@@ -37,12 +37,13 @@
 // loads, 94.5 us = 5.7 TB/s with plain ones (108 us with the dot products, G softmaxes
 // per row in 16 lanes each and G x 128 multiply-adds per row on the vector ALU; that form
 // was vector-bound at G = 8).
-// Work split: the segments' rows, in chunks of 64, are dealt out evenly to one round of
-// resident workgroups, whatever the lengths of the segments (the lengths are on the
-// device: every workgroup derives its own share from them).  A share may end one segment
-// and begin the next (three segments of 24 to 45 k tokens x 8 KV heads, G = 8: 83 -> 73.5
-// us against equal ranges of the longest segment).  The partials (m, l, acc[128]) of the pieces of a segment are
-// merged by a second small kernel: no counters, no atomics.
+// Work split: up to kDealtSegs segments, their rows, in chunks of 64, are dealt out evenly to one round of resident
+// workgroups, whatever the lengths of the segments (the lengths are on the device: every wave derives its share from
+// them).  A share may end one segment and begin the next (three segments of 24 to 45 k tokens x 8 KV heads, G = 8: 83 ->
+// 73.5 us against equal ranges of the longest segment).  More segments fill the chip by themselves: each is cut into
+// equal ranges of at least kRangeRows rows, and the lookup, which would cost every workgroup more than its rows do,
+// falls away.  A segment that is one range is finished by its workgroup.
+// The partials (m, l, acc[128]) of the pieces of a segment are merged by a second small kernel: no counters, no atomics.
 #include "dp_attend.hpp"
 #include "dp_device.hpp"
 #include "dp_kernels.hpp"
@@ -68,37 +69,84 @@ struct DenseArgs {
   float *lse;  // nullable
   int32_t n_seg, n_kv_heads, n_q_heads, group;
   int32_t head0;  // this launch serves heads [head0, head0 + 16) of every group
-  int32_t splits, min_share, grid, max_rows, out_is_bf16;
+  int32_t splits;            // partial slots per head
+  int32_t min_share, grid;   // chunks dealt out: fewest per workgroup, workgroups
+  int32_t ranges;            // > 0: every segment cut into at most so many ranges instead
+  int32_t max_rows, out_is_bf16;
   float scale_log2;
 };
 
-// How the chunks (kChunkRows rows) of all segments, numbered through in segment order, are dealt out: workgroup w
-// takes chunks [w share, (w + 1) share).
-struct DenseShare {
-  int total, share;
-};
+// Dealt out up to here (16 segments per lane in the lookup).  Cut by themselves, with the lookup in front of every
+// workgroup's rows: 2048 segments of 64 rows 23.9 against 86.4 us, of 1024 rows 165 / 234; at 512 segments of 64 to 4071
+// rows dealing is still the faster one (118 us; 153 for equal ranges of the longest).
+constexpr int kDealtSegs = 1024;
+constexpr int kRangeRows = 1024;
 
-// Call with the whole workgroup of T threads; s_scan: T / 64 + 1 ints of LDS.  find(seg, first chunk, chunks of seg) is
-// called once for every segment that has rows, each by some thread.
-template <int T, class F>
-__device__ __forceinline__ DenseShare dense_share(const DenseArgs &a, int *s_scan, F find) {
-  const int per = (a.n_seg + T - 1) / T;  // consecutive segments per thread
+__device__ __forceinline__ int dense_rows(const DenseArgs &a, int seg) { return max(0, min(a.seg_rows[seg], a.max_rows)); }
+__device__ __forceinline__ int dense_chunks(int rows) { return (rows + kChunkRows - 1) / kChunkRows; }
+
+// The chunks of all segments, numbered through in segment order: workgroup w takes chunks [w share, (w + 1) share).
+__device__ __forceinline__ int dealt_share(const DenseArgs &a, int total) {
+  return max(a.min_share, (total + a.grid - 1) / a.grid);
+}
+// The chunks of one segment in equal ranges: range r takes [r share, (r + 1) share).
+__device__ __forceinline__ int range_share(const DenseArgs &a, int chunks) {
+  const int n = max(1, min(a.ranges, chunks / (kRangeRows / kChunkRows)));
+  return max(1, (chunks + n - 1) / n);
+}
+
+// The segment that holds chunk c = blockIdx.x * share, by every wave for itself: a lane adds up `per` consecutive
+// segments, then the lane that holds the chunk has its segments spread over the lanes.  false: no chunk is left.
+struct DenseStart {
+  int seg, first, c, c_end;  // segment, its first chunk; the workgroup's chunks
+  int share;
+};
+__device__ __forceinline__ bool dense_start(const DenseArgs &a, DenseStart &d) {
+  const int lane = lane_id(), per = (a.n_seg + 63) / 64;
   int mine = 0;
+#pragma unroll 4
   for (int u = 0; u < per; ++u) {
-    const int seg = threadIdx.x * per + u;
-    if (seg < a.n_seg) mine += (max(0, min(a.seg_rows[seg], a.max_rows)) + kChunkRows - 1) / kChunkRows;
+    const int seg = lane * per + u, rows = dense_rows(a, min(seg, a.n_seg - 1));
+    mine += seg < a.n_seg ? dense_chunks(rows) : 0;
   }
-  DenseShare d;
-  int run = block_excl_scan<int, T / 64>(mine, s_scan, d.total);
-  d.share = max(a.min_share, (d.total + a.grid - 1) / a.grid);
-  for (int u = 0; u < per; ++u) {
-    const int seg = threadIdx.x * per + u;
-    if (seg >= a.n_seg) break;
-    const int chunks = (max(0, min(a.seg_rows[seg], a.max_rows)) + kChunkRows - 1) / kChunkRows;
-    if (chunks > 0) find(seg, run, chunks, d.share);
-    run += chunks;
+  int upto = wave_incl_scan(mine);
+  const int total = (int)lane_u32((uint32_t)upto, 63);
+  d.share = dealt_share(a, total);
+  d.c = blockIdx.x * d.share;
+  d.c_end = min(total, d.c + d.share);
+  if (d.c >= d.c_end) return false;
+  int at = __builtin_ctzll(__ballot(upto - mine <= d.c && d.c < upto));
+  d.seg = at * per;
+  d.first = (int)lane_u32((uint32_t)(upto - mine), at);
+  if (per > 1) {
+    const int seg = d.seg + lane, rows = dense_rows(a, min(seg, a.n_seg - 1));
+    mine = lane < per && seg < a.n_seg ? dense_chunks(rows) : 0;
+    upto = d.first + wave_incl_scan(mine);
+    at = __builtin_ctzll(__ballot(upto - mine <= d.c && d.c < upto));
+    d.seg += at;
+    d.first = (int)lane_u32((uint32_t)(upto - mine), at);
   }
-  return d;
+  return true;
+}
+
+// Number of pieces of segment my_seg (which has rows), by every wave for itself.
+__device__ __forceinline__ int dense_pieces(const DenseArgs &a, int my_seg, int chunks) {
+  if (a.ranges > 0) {
+    const int share = range_share(a, chunks);
+    return (chunks + share - 1) / share;
+  }
+  int total = 0, first = 0;
+#pragma unroll 4
+  for (int u = 0; u < a.n_seg; u += 64) {
+    const int seg = u + lane_id(), rows = dense_rows(a, min(seg, a.n_seg - 1));
+    const int n = seg < a.n_seg ? dense_chunks(rows) : 0;
+    total += n;
+    first += seg < my_seg ? n : 0;
+  }
+  total = wave_sum(total);
+  first = wave_sum(first);
+  const int share = dealt_share(a, total);
+  return (first + chunks - 1) / share - first / share + 1;
 }
 
 // what is subtracted from a score whose running maximum is m
@@ -127,30 +175,42 @@ __device__ __forceinline__ void load_dense_tile(const DenseArgs &a, int64_t row0
 __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void dense_kernel(DenseArgs a) {
   __shared__ float s_m[kDenseWaves][kDenseHeads], s_l[kDenseWaves][kDenseHeads];
   __shared__ __align__(16) float s_acc[kDenseWaves][kDenseHeads][kHeadDim + 4];
-  __shared__ int s_scan[kDenseWaves + 1], s_seg, s_first;
   const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
   const int r = lane & 15, kq = lane >> 4;
-  const DenseShare dealt = dense_share<kDenseThreads>(a, s_scan, [&](int seg, int first, int chunks, int share) {
-    const int c = blockIdx.x * share;
-    if (first <= c && c < first + chunks) {  // the segment that holds the first chunk of this workgroup
-      s_seg = seg;
-      s_first = first;
+  DenseStart at;
+  int number = blockIdx.x;  // of the share, or of the range inside the segment
+  if (a.ranges > 0) {
+    at.seg = blockIdx.x / a.ranges;
+    number = blockIdx.x % a.ranges;
+    const int chunks = dense_chunks(dense_rows(a, at.seg));
+    if (chunks == 0 && a.ranges == 1) {  // no rows, and no merge follows: zero output
+      const int b = at.seg / a.n_kv_heads, g = at.seg % a.n_kv_heads;
+      const int64_t head = (int64_t)b * a.n_q_heads + g * a.group + a.head0;
+      const int n_live = min(kDenseHeads, a.group - a.head0);
+      for (int j = tid / kHeadDim; j < n_live; j += kDenseThreads / kHeadDim) {
+        store_out(a.out, a.out_is_bf16, head + j, tid % kHeadDim, 0.f);
+        if (a.lse && tid % kHeadDim == 0) a.lse[head + j] = -INFINITY;
+      }
     }
-  });
-  int c0 = blockIdx.x * dealt.share;
-  const int c_end = min(dealt.total, c0 + dealt.share);
-  if (c0 >= c_end) return;
-  __syncthreads();
-  int seg = s_seg, first = s_first;
+    at.first = 0;
+    at.share = range_share(a, chunks);
+    at.c = number * at.share;
+    at.c_end = min(chunks, at.c + at.share);
+    if (at.c >= at.c_end) return;
+  } else if (!dense_start(a, at)) {
+    return;
+  }
+  int seg = at.seg, first = at.first, c0 = at.c;
+  const int c_end = at.c_end, share = at.share;
   const int n_live = min(kDenseHeads, a.group - a.head0);
 
   // one piece of a segment after the other, usually one
   for (; c0 < c_end; ++seg) {
-    const int R = max(0, min(a.seg_rows[seg], a.max_rows));
+    const int R = dense_rows(a, seg);
     if (R == 0) continue;
-    const int seg_end = first + (R + kChunkRows - 1) / kChunkRows;
+    const int seg_end = first + dense_chunks(R);
     const int ra = (c0 - first) * kChunkRows, rb = min(R, (min(c_end, seg_end) - first) * kChunkRows);
-    const int split = blockIdx.x - first / dealt.share;  // number of the piece inside its segment
+    const int split = number - first / share;  // number of the piece inside its segment
     c0 = seg_end;
     first = seg_end;
     const int b = seg / a.n_kv_heads, g = seg % a.n_kv_heads;
@@ -259,6 +319,11 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
         L += s_l[w][j] * wg;
         o += s_acc[w][j][d] * wg;
       }
+      if (a.ranges == 1) {
+        store_out(a.out, a.out_is_bf16, head_first + j, d, o / L);
+        if (a.lse && d == 0) a.lse[head_first + j] = (M + log2f(L)) * kLn2;
+        continue;
+      }
       float *P = a.partials + ((head_first + j) * a.splits + split) * kPartialStride;
       if (d == 0) {
         P[0] = M;
@@ -270,37 +335,31 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
   }
 }
 
-// One workgroup per head; its eight groups of 128 threads (one dimension each) take the splits in turn, so that the
-// partials of a head are fetched in a round or two of loads, and meet in LDS.  (One group walking all splits of a head
-// eight at a time took 20 us for the 96 splits of 8 x 131072 tokens: a dozen dependent round trips on 32 CUs.)
-constexpr int kMergeGroups = 8;
-__global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(DenseArgs a) {
-  __shared__ float s_m[kMergeGroups], s_l[kMergeGroups], s_o[kMergeGroups][kHeadDim];
-  __shared__ int s_scan[kMergeGroups * kHeadDim / 64 + 1], s_pieces;
+// One workgroup per head; its groups of 128 threads (one dimension each) take the splits in turn, so that the partials
+// of a head are fetched in a round or two of loads, and meet in LDS.  (One group walking all splits of a head eight at
+// a time took 20 us for the 96 splits of 8 x 131072 tokens: a dozen dependent round trips on 32 CUs.)
+template <int kGroups>
+__global__ __launch_bounds__(kGroups * kHeadDim) void dense_merge_kernel(DenseArgs a) {
+  __shared__ float s_m[kGroups], s_l[kGroups], s_o[kGroups][kHeadDim];
   const int head = blockIdx.x, t = threadIdx.x % kHeadDim, grp = threadIdx.x / kHeadDim;
   const int b = head / a.n_q_heads, h = head % a.n_q_heads;
-  const int my_seg = b * a.n_kv_heads + h / a.group;
-  if (threadIdx.x == 0) s_pieces = 0;
-  __syncthreads();
-  dense_share<kMergeGroups * kHeadDim>(a, s_scan, [&](int seg, int first, int chunks, int share) {
-    if (seg == my_seg) s_pieces = (first + chunks - 1) / share - first / share + 1;
-  });
-  __syncthreads();
-  const int n_active = s_pieces;
-  if (n_active <= 0) {  // an empty segment: zero output
+  const int seg = b * a.n_kv_heads + h / a.group;
+  const int chunks = dense_chunks(dense_rows(a, seg));
+  if (chunks == 0) {  // an empty segment: zero output
     if (grp > 0) return;
     store_out(a.out, a.out_is_bf16, head, t, 0.f);
     if (a.lse && t == 0) a.lse[head] = -INFINITY;
     return;
   }
+  const int n_active = dense_pieces(a, seg, chunks);
   const float *P = a.partials + (int64_t)head * a.splits * kPartialStride;
   constexpr int kBatch = 8;
   float Mx = -INFINITY, Ls = 0.f, os = 0.f;
-  for (int s0 = grp; s0 < n_active; s0 += kMergeGroups * kBatch) {
+  for (int s0 = grp; s0 < n_active; s0 += kGroups * kBatch) {
     float ms[kBatch], ll[kBatch], oo[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const float *Q = P + min(s0 + kMergeGroups * u, n_active - 1) * kPartialStride;
+      const float *Q = P + min(s0 + kGroups * u, n_active - 1) * kPartialStride;
       ms[u] = Q[0];
       ll[u] = Q[1];
       oo[u] = Q[2 + t];
@@ -308,7 +367,7 @@ __global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(De
     float Mn = Mx;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (s0 + kMergeGroups * u >= n_active) {
+      if (s0 + kGroups * u >= n_active) {
         ms[u] = -INFINITY;
         ll[u] = oo[u] = 0.f;
       }
@@ -334,9 +393,9 @@ __global__ __launch_bounds__(kMergeGroups * kHeadDim) void dense_merge_kernel(De
   if (grp > 0) return;
   float M = s_m[0], L = 0.f, o = 0.f;  // the first group has at least one split
 #pragma unroll
-  for (int v = 1; v < kMergeGroups; ++v) M = fmaxf(M, s_m[v]);
+  for (int v = 1; v < kGroups; ++v) M = fmaxf(M, s_m[v]);
 #pragma unroll
-  for (int v = 0; v < kMergeGroups; ++v) {
+  for (int v = 0; v < kGroups; ++v) {
     const float w = exp2f(s_m[v] - finite_max(M));
     L = fmaf(s_l[v], w, L);
     o = fmaf(s_o[v][t], w, o);
@@ -383,13 +442,27 @@ hipError_t launch_dense(const CacheView &c, const int32_t *seg_rows, float *part
   }
   const long want = ((long)n_seg * max_chunks + a.min_share - 1) / a.min_share;
   a.grid = (int)(want < 1 ? 1 : want < kResident ? want : kResident);
-  if (c.max_rows_per_seg > 0) {
+  a.ranges = 0;
+  int blocks = a.grid;
+  if (n_seg > kDealtSegs) {
+    const int most = max_chunks / (kRangeRows / kChunkRows);
+    a.ranges = most < 1 ? 1 : most < max_splits ? most : max_splits;
+    blocks = n_seg * a.ranges;
+  }
+  if (c.max_rows_per_seg > 0 || a.ranges == 1) {
     for (int h0 = 0; h0 < c.group; h0 += kDenseHeads) {  // one pass over the cache for up to 16 heads of a group
       a.head0 = h0;
-      hipLaunchKernelGGL(dense_kernel, dim3(a.grid), dim3(kDenseThreads), 0, s, a);
+      hipLaunchKernelGGL(dense_kernel, dim3(blocks), dim3(kDenseThreads), 0, s, a);
     }
   }
-  hipLaunchKernelGGL(dense_merge_kernel, dim3(nh), dim3(kMergeGroups * kHeadDim), 0, s, a);
+  if (a.ranges == 1) return hipGetLastError();
+  // From 512 heads on a head has at most 32 partial slots, four rounds of loads for one group of threads, and the heads
+  // fill the chip.  One group against eight: 512 heads (16 x 2048 tokens) 29.5 against 31.5 us for the call, 1024 heads
+  // 47.9 / 52.4, 4096 heads (64 x 1024) 54.9 / 74.0.  (Few heads with many slots: at the kernel.)
+  if (nh >= 512)
+    hipLaunchKernelGGL(dense_merge_kernel<1>, dim3(nh), dim3(kHeadDim), 0, s, a);
+  else
+    hipLaunchKernelGGL(dense_merge_kernel<8>, dim3(nh), dim3(8 * kHeadDim), 0, s, a);
   return hipGetLastError();
 }
 

@@ -39,6 +39,24 @@ def test_dense_decode_deals_rows_out_over_ragged_segments():
     assert np.abs(lse - ref_lse)[~empty].max() <= 2e-5 * np.abs(ref_lse).max()
 
 
+@pytest.mark.parametrize("n_seg", [64, 65, 1024, 1025])
+def test_dense_decode_of_many_segments(n_seg):
+    """Lengths looked up by one lane each, by several lanes, and not at all (every segment cut by itself); segments of
+    none to 1100 rows, so shares that hold several segments and segments that hold several shares."""
+    rng = np.random.default_rng(n_seg)
+    ctx = [int(x) for x in rng.choice([1, 16, 63, 64, 65, 129, 511, 513, 1100], size=n_seg)]
+    c = make_cache(batch=n_seg, n_kv_heads=1, n_q_heads=2, context=ctx, mean_cluster=64, size_hi=256, q_scale=0.7, seed=67)
+    rows = H.segment_rows(c)
+    rows[rng.choice(n_seg, 9, replace=False)] = 0
+    rows[0], rows[-1] = 0, ctx[-1]
+    out, lse = H.gpu_dense_decode(c, rows)
+    ref, ref_lse, _ = oracle.Oracle(c).dense_step(n_threads=4)
+    full = rows > 0
+    assert (out[~full] == 0).all() and np.isneginf(lse[~full]).all()
+    assert np.abs(out - ref)[full].max() <= 2e-5
+    assert np.abs(lse - ref_lse)[full].max() <= 2e-5 * np.abs(ref_lse).max()
+
+
 BF16 = {"inf": 0x7F80, "-inf": 0xFF80, "one": 0x3F80, "huge": 0x7F62}   # huge = 3.004e38
 
 
