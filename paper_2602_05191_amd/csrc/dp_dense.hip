@@ -37,13 +37,14 @@
 // loads, 94.5 us = 5.7 TB/s with plain ones (108 us with the dot products, G softmaxes
 // per row in 16 lanes each and G x 128 multiply-adds per row on the vector ALU; that form
 // was vector-bound at G = 8).
-// Work split: up to kDealtSegs segments, their rows, in chunks of 64, are dealt out evenly to one round of resident
-// workgroups, whatever the lengths of the segments (the lengths are on the device: every wave derives its share from
-// them).  A share may end one segment and begin the next (three segments of 24 to 45 k tokens x 8 KV heads, G = 8: 83 ->
-// 73.5 us against equal ranges of the longest segment).  More segments fill the chip by themselves: each is cut into
-// equal ranges of at least kRangeRows rows, and the lookup, which would cost every workgroup more than its rows do,
-// falls away.  A segment that is one range is finished by its workgroup.
-// The partials (m, l, acc[128]) of the pieces of a segment are merged by a second small kernel: no counters, no atomics.
+// Work split: the segments' rows, in chunks of 64, are dealt out evenly to one round of resident workgroups, whatever
+// the lengths of the segments (the lengths are on the device: every wave derives its share from them).  A share may end
+// one segment and begin the next (three segments of 24 to 45 k tokens x 8 KV heads, G = 8: 83 -> 73.5 us against equal
+// ranges of the longest segment).  The partials (m, l, acc[128]) of the pieces of a segment are merged by a second small
+// kernel: no counters, no atomics.  Short or very many segments are taken whole, a workgroup each, which then writes the
+// output itself: one launch.
+#include <type_traits>
+
 #include "dp_attend.hpp"
 #include "dp_device.hpp"
 #include "dp_kernels.hpp"
@@ -71,16 +72,12 @@ struct DenseArgs {
   int32_t head0;  // this launch serves heads [head0, head0 + 16) of every group
   int32_t splits;            // partial slots per head
   int32_t min_share, grid;   // chunks dealt out: fewest per workgroup, workgroups
-  int32_t ranges;            // > 0: every segment cut into at most so many ranges instead
+  int32_t whole;             // nothing dealt out: a workgroup per segment
   int32_t max_rows, out_is_bf16;
   float scale_log2;
 };
 
-// Dealt out up to here (16 segments per lane in the lookup).  Cut by themselves, with the lookup in front of every
-// workgroup's rows: 2048 segments of 64 rows 23.9 against 86.4 us, of 1024 rows 165 / 234; at 512 segments of 64 to 4071
-// rows dealing is still the faster one (118 us; 153 for equal ranges of the longest).
-constexpr int kDealtSegs = 1024;
-constexpr int kRangeRows = 1024;
+constexpr int kDealtSegs = 64 * 64;  // most segments that the lookup can hold
 
 __device__ __forceinline__ int dense_rows(const DenseArgs &a, int seg) { return max(0, min(a.seg_rows[seg], a.max_rows)); }
 __device__ __forceinline__ int dense_chunks(int rows) { return (rows + kChunkRows - 1) / kChunkRows; }
@@ -89,25 +86,32 @@ __device__ __forceinline__ int dense_chunks(int rows) { return (rows + kChunkRow
 __device__ __forceinline__ int dealt_share(const DenseArgs &a, int total) {
   return max(a.min_share, (total + a.grid - 1) / a.grid);
 }
-// The chunks of one segment in equal ranges: range r takes [r share, (r + 1) share).
-__device__ __forceinline__ int range_share(const DenseArgs &a, int chunks) {
-  const int n = max(1, min(a.ranges, chunks / (kRangeRows / kChunkRows)));
-  return max(1, (chunks + n - 1) / n);
-}
-
 // The segment that holds chunk c = blockIdx.x * share, by every wave for itself: a lane adds up `per` consecutive
-// segments, then the lane that holds the chunk has its segments spread over the lanes.  false: no chunk is left.
+// segments, then the lane that holds the chunk has its segments spread over the lanes.  The row base comes along, so that
+// nothing but the rows themselves is left to wait for.  false: no chunk is left.
 struct DenseStart {
-  int seg, first, c, c_end;  // segment, its first chunk; the workgroup's chunks
-  int share;
+  int seg, first, rows;  // segment, its first chunk, its rows
+  int64_t row0;
+  int c, c_end, share;   // the workgroup's chunks
 };
 __device__ __forceinline__ bool dense_start(const DenseArgs &a, DenseStart &d) {
   const int lane = lane_id(), per = (a.n_seg + 63) / 64;
-  int mine = 0;
+  int rows = 0, mine = 0;
+  int64_t base = 0;
+  auto look = [&](int seg, bool valid) {
+    const int s = min(seg, a.n_seg - 1);
+    rows = dense_rows(a, s);
+    base = a.seg_row_base[s];
+    return valid && seg < a.n_seg ? dense_chunks(rows) : 0;
+  };
+  if (per == 1) {
+    mine = look(lane, true);
+  } else {
 #pragma unroll 4
-  for (int u = 0; u < per; ++u) {
-    const int seg = lane * per + u, rows = dense_rows(a, min(seg, a.n_seg - 1));
-    mine += seg < a.n_seg ? dense_chunks(rows) : 0;
+    for (int u = 0; u < per; ++u) {
+      const int seg = lane * per + u, n = dense_chunks(dense_rows(a, min(seg, a.n_seg - 1)));
+      mine += seg < a.n_seg ? n : 0;
+    }
   }
   int upto = wave_incl_scan(mine);
   const int total = (int)lane_u32((uint32_t)upto, 63);
@@ -119,22 +123,19 @@ __device__ __forceinline__ bool dense_start(const DenseArgs &a, DenseStart &d) {
   d.seg = at * per;
   d.first = (int)lane_u32((uint32_t)(upto - mine), at);
   if (per > 1) {
-    const int seg = d.seg + lane, rows = dense_rows(a, min(seg, a.n_seg - 1));
-    mine = lane < per && seg < a.n_seg ? dense_chunks(rows) : 0;
+    mine = look(d.seg + lane, lane < per);
     upto = d.first + wave_incl_scan(mine);
     at = __builtin_ctzll(__ballot(upto - mine <= d.c && d.c < upto));
     d.seg += at;
     d.first = (int)lane_u32((uint32_t)(upto - mine), at);
   }
+  d.rows = (int)lane_u32((uint32_t)rows, at);
+  d.row0 = (int64_t)lane_u64((unsigned long long)base, at);
   return true;
 }
 
 // Number of pieces of segment my_seg (which has rows), by every wave for itself.
 __device__ __forceinline__ int dense_pieces(const DenseArgs &a, int my_seg, int chunks) {
-  if (a.ranges > 0) {
-    const int share = range_share(a, chunks);
-    return (chunks + share - 1) / share;
-  }
   int total = 0, first = 0;
 #pragma unroll 4
   for (int u = 0; u < a.n_seg; u += 64) {
@@ -177,60 +178,55 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
   __shared__ __align__(16) float s_acc[kDenseWaves][kDenseHeads][kHeadDim + 4];
   const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
   const int r = lane & 15, kq = lane >> 4;
+  const int n_live = min(kDenseHeads, a.group - a.head0);
   DenseStart at;
-  int number = blockIdx.x;  // of the share, or of the range inside the segment
-  if (a.ranges > 0) {
-    at.seg = blockIdx.x / a.ranges;
-    number = blockIdx.x % a.ranges;
-    const int chunks = dense_chunks(dense_rows(a, at.seg));
-    if (chunks == 0 && a.ranges == 1) {  // no rows, and no merge follows: zero output
-      const int b = at.seg / a.n_kv_heads, g = at.seg % a.n_kv_heads;
-      const int64_t head = (int64_t)b * a.n_q_heads + g * a.group + a.head0;
-      const int n_live = min(kDenseHeads, a.group - a.head0);
+  if (a.whole) {
+    at.seg = blockIdx.x;
+    at.rows = dense_rows(a, at.seg);
+    at.row0 = a.seg_row_base[at.seg];
+    at.first = at.c = 0;
+    at.c_end = dense_chunks(at.rows);
+    at.share = 1;
+    if (at.rows == 0) {  // zero output
+      const int64_t head = (int64_t)(at.seg / a.n_kv_heads) * a.n_q_heads + at.seg % a.n_kv_heads * a.group + a.head0;
       for (int j = tid / kHeadDim; j < n_live; j += kDenseThreads / kHeadDim) {
         store_out(a.out, a.out_is_bf16, head + j, tid % kHeadDim, 0.f);
         if (a.lse && tid % kHeadDim == 0) a.lse[head + j] = -INFINITY;
       }
+      return;
     }
-    at.first = 0;
-    at.share = range_share(a, chunks);
-    at.c = number * at.share;
-    at.c_end = min(chunks, at.c + at.share);
-    if (at.c >= at.c_end) return;
   } else if (!dense_start(a, at)) {
     return;
   }
-  int seg = at.seg, first = at.first, c0 = at.c;
+  int seg = at.seg, first = at.first, R = at.rows, c0 = at.c;
+  int64_t row0 = at.row0;
   const int c_end = at.c_end, share = at.share;
-  const int n_live = min(kDenseHeads, a.group - a.head0);
 
   // one piece of a segment after the other, usually one
-  for (; c0 < c_end; ++seg) {
-    const int R = dense_rows(a, seg);
-    if (R == 0) continue;
+  while (true) {
     const int seg_end = first + dense_chunks(R);
     const int ra = (c0 - first) * kChunkRows, rb = min(R, (min(c_end, seg_end) - first) * kChunkRows);
-    const int split = number - first / share;  // number of the piece inside its segment
+    const int split = blockIdx.x - first / share;  // number of the piece inside its segment
     c0 = seg_end;
     first = seg_end;
     const int b = seg / a.n_kv_heads, g = seg % a.n_kv_heads;
     const int64_t head_first = (int64_t)b * a.n_q_heads + g * a.group + a.head0;
-    const int64_t row0 = a.seg_row_base[seg];
 
-    // query head r of the pass (a zero column beyond the group), chunks kq + 4 j
+    // query head r of the pass (beyond the group: its last head again, not stored), chunks kq + 4 j
     uint4 Q[4];
     {
       const char *row = static_cast<const char *>(a.q) + (head_first + min(r, n_live - 1)) * kRowBytes + kq * 16;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        Q[j] = r < n_live ? *reinterpret_cast<const uint4 *>(row + j * 64) : make_uint4(0, 0, 0, 0);
+        Q[j] = *reinterpret_cast<const uint4 *>(row + j * 64);
     }
     f32x4 acc[8];
 #pragma unroll
     for (int n = 0; n < 8; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;  // head r: the maximum of all rows so far, the weights of this lane's rows
 
-    auto attend = [&](DenseTile &d, int t) {
+    // (rows beyond the range exist in a wave's last tile only)
+    auto attend = [&](DenseTile &d, int t, auto last) {
       const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
       f32x4 part[4];
 #pragma unroll
@@ -238,8 +234,10 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
         part[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, d.k[j]),
                                                           __builtin_bit_cast(bf16x8, Q[j]), zero, 0, 0, 0);
       f32x4 x = (part[0] + part[1]) + (part[2] + part[3]);  // unscaled
+      if constexpr (last) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = t + 4 * kq + i < rb ? x[i] : -INFINITY;
+        for (int i = 0; i < 4; ++i) x[i] = t + 4 * kq + i < rb ? x[i] : -INFINITY;
+      }
       float top = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
       top = fmaxf(top, xor16(top));
       top = fmaxf(top, xor32(top));
@@ -255,7 +253,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[i] = exp2f(fmaf(x[i], a.scale_log2, -sub));
       l += (x[0] + x[1]) + (x[2] + x[3]);
-      if (t + kDenseTile > rb) {
+      if constexpr (last) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (t + 4 * kq + i >= rb) d.v[i] = make_uint4(0, 0, 0, 0);
@@ -274,20 +272,29 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     };
 
     // the workgroup's waves take tiles in turn; the next tile's loads are in flight during a tile's arithmetic
+    // (none is issued behind the last one: 2048 tokens x 8 KV heads 11.2 -> 10.2 us)
     constexpr int kStep = kDenseWaves * kDenseTile;
     int t = ra + wave * kDenseTile;
+    constexpr std::integral_constant<bool, false> kFull{};
+    constexpr std::integral_constant<bool, true> kLast{};
     if (t < rb) {
       DenseTile d0, d1;
       load_dense_tile(a, row0, t, rb - 1, r, kq, d0);
       while (true) {
+        if (t + kStep >= rb) {
+          attend(d0, t, kLast);
+          break;
+        }
         load_dense_tile(a, row0, t + kStep, rb - 1, r, kq, d1);
-        attend(d0, t);
+        attend(d0, t, kFull);
         t += kStep;
-        if (t >= rb) break;
+        if (t + kStep >= rb) {
+          attend(d1, t, kLast);
+          break;
+        }
         load_dense_tile(a, row0, t + kStep, rb - 1, r, kq, d0);
-        attend(d1, t);
+        attend(d1, t, kFull);
         t += kStep;
-        if (t >= rb) break;
       }
     }
     l += xor16(l);
@@ -319,7 +326,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
         L += s_l[w][j] * wg;
         o += s_acc[w][j][d] * wg;
       }
-      if (a.ranges == 1) {
+      if (a.whole) {
         store_out(a.out, a.out_is_bf16, head_first + j, d, o / L);
         if (a.lse && d == 0) a.lse[head_first + j] = (M + log2f(L)) * kLn2;
         continue;
@@ -331,7 +338,11 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
       }
       P[2 + d] = o;
     }
+    if (c0 >= c_end) break;
     __syncthreads();  // LDS is reused by the next piece
+    do R = dense_rows(a, ++seg);
+    while (R == 0);  // (a segment with rows follows: chunks are left)
+    row0 = a.seg_row_base[seg];
   }
 }
 
@@ -442,20 +453,17 @@ hipError_t launch_dense(const CacheView &c, const int32_t *seg_rows, float *part
   }
   const long want = ((long)n_seg * max_chunks + a.min_share - 1) / a.min_share;
   a.grid = (int)(want < 1 ? 1 : want < kResident ? want : kResident);
-  a.ranges = 0;
-  int blocks = a.grid;
-  if (n_seg > kDealtSegs) {
-    const int most = max_chunks / (kRangeRows / kChunkRows);
-    a.ranges = most < 1 ? 1 : most < max_splits ? most : max_splits;
-    blocks = n_seg * a.ranges;
-  }
-  if (c.max_rows_per_seg > 0 || a.ranges == 1) {
+  // Whole segments against dealt-out chunks (us; G = 4): 8 segments of 320 rows 8.8 / 11.0, of 512 11.8 / 11.0; 128 of 512
+  // 12.6 / 13.4, 320 of 512 22.1 / 23.3, 320 of 1024 39 / 36; 512 of 1024 42.6 / 50.0, 2048 of 64 20 / 57 with the lookup
+  // in front of every workgroup.  Longer segments are dealt out (512 of 512 to 2048: 66 / 116) as far as the lookup goes.
+  a.whole = n_seg > kDealtSegs || c.max_rows_per_seg <= (n_seg >= 512 ? 1024 : n_seg >= 128 ? 512 : 320);
+  if (c.max_rows_per_seg > 0 || a.whole) {
     for (int h0 = 0; h0 < c.group; h0 += kDenseHeads) {  // one pass over the cache for up to 16 heads of a group
       a.head0 = h0;
-      hipLaunchKernelGGL(dense_kernel, dim3(blocks), dim3(kDenseThreads), 0, s, a);
+      hipLaunchKernelGGL(dense_kernel, dim3(a.whole ? n_seg : a.grid), dim3(kDenseThreads), 0, s, a);
     }
   }
-  if (a.ranges == 1) return hipGetLastError();
+  if (a.whole) return hipGetLastError();
   // From 512 heads on a head has at most 32 partial slots, four rounds of loads for one group of threads, and the heads
   // fill the chip.  One group against eight: 512 heads (16 x 2048 tokens) 29.5 against 31.5 us for the call, 1024 heads
   // 47.9 / 52.4, 4096 heads (64 x 1024) 54.9 / 74.0.  (Few heads with many slots: at the kernel.)

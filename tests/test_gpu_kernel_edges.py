@@ -39,16 +39,21 @@ def test_dense_decode_deals_rows_out_over_ragged_segments():
     assert np.abs(lse - ref_lse)[~empty].max() <= 2e-5 * np.abs(ref_lse).max()
 
 
-@pytest.mark.parametrize("n_seg", [64, 65, 1024, 1025])
-def test_dense_decode_of_many_segments(n_seg):
-    """Lengths looked up by one lane each, by several lanes, and not at all (every segment cut by itself); segments of
-    none to 1100 rows, so shares that hold several segments and segments that hold several shares."""
+@pytest.mark.parametrize("n_seg, lengths", [
+    (9, [1, 320]), (9, [1, 321]), (127, [17, 64, 512]), (128, [17, 64, 512]), (128, [16, 513]), (511, [1, 65, 1024]),
+    (512, [1, 65, 1024]), (512, [1, 63, 1025]), (64, [1, 64, 129, 1500]), (65, [1, 64, 129, 1500]), (4096, [1, 2, 1030]),
+    (4097, [1, 2, 1030])])
+def test_dense_decode_of_many_segments(n_seg, lengths):
+    """Segments taken whole by a workgroup and segments whose chunks are dealt out, at the lengths and counts where one
+    form ends; looked up by one lane each, by several, by all; segments without rows."""
     rng = np.random.default_rng(n_seg)
-    ctx = [int(x) for x in rng.choice([1, 16, 63, 64, 65, 129, 511, 513, 1100], size=n_seg)]
+    ctx = [int(x) for x in rng.choice(lengths, size=n_seg)]
+    if n_seg > 4000:   # (few long ones)
+        ctx = [n if n < 1000 or i % 97 == 0 else 3 for i, n in enumerate(ctx)]
+    ctx[-1] = max(lengths)
     c = make_cache(batch=n_seg, n_kv_heads=1, n_q_heads=2, context=ctx, mean_cluster=64, size_hi=256, q_scale=0.7, seed=67)
     rows = H.segment_rows(c)
-    rows[rng.choice(n_seg, 9, replace=False)] = 0
-    rows[0], rows[-1] = 0, ctx[-1]
+    rows[rng.choice(n_seg - 1, n_seg // 8, replace=False)] = 0
     out, lse = H.gpu_dense_decode(c, rows)
     ref, ref_lse, _ = oracle.Oracle(c).dense_step(n_threads=4)
     full = rows > 0
