@@ -204,6 +204,10 @@ __device__ __forceinline__ uint32_t f64_to_bf16_rne(double x) {
 // place; the next chunk's rows are fetched while the chunk is summed.  Thread d sums column d (key dimensions, then
 // value dimensions) of the chunk's rows in row order, in fp64, and writes a cluster's means when its last row has gone
 // by.  A sum carries over from chunk to chunk.
+// One long run is one workgroup's serial work (a cluster of 131072 of 1 M tokens: 2048 chunks of 2.2 us), so nothing in it
+// may wait in turn: the list is read in batches, one ahead, the tokens of a chunk come a chunk before its rows and the
+// rows a chunk before they are summed (all tokens of 8 segments in one cluster each: 6311 -> 4610 us; half of them 3812 ->
+// 2827; with the list read in front of every chunk's rows these were slower than the one-level sort: 5330, 2850).
 // Rows go by once: non-temporal loads and stores (move of 8 x 131072 tokens 228 -> 215 us = 5.2 TB/s over 1.11 GB; a
 // plain copy of 2 GB runs at 4.7 TB/s on the same card).
 // kMove = false: keys only (the update step of k-means): nothing is stored in place, no value is read, the two halves
@@ -249,26 +253,34 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
     for (int b = 0; b < 4; ++b) s.bit[b] = __ballot((word >> b) & 1);
     return s;
   };
-  constexpr int kKeep = 2;  // list entries per lane that stay in registers from the first pass to the second
+  // The wave's share, 64 words at a time: the first kKeep of a lane stay in registers from the first pass to the second,
+  // the others are loaded kAhead at a time, one batch ahead.
+  constexpr int kKeep = 2, kAhead = 8;
   uint64_t kept[kKeep];
-  int count = 0;
+  auto word_at = [&](int u) { return binned[min(j0 + 64 * u + lane, n_run - 1)]; };
 #pragma unroll
-  for (int u = 0; u < kKeep; ++u) {
-    const int j = j0 + 64 * u + lane;
-    kept[u] = n_run > 0 ? binned[min(j, n_run - 1)] : 0;
-  }
-  auto word_of = [&](int u) {
-    uint64_t w = 0;
+  for (int u = 0; u < kKeep; ++u) kept[u] = n_run > 0 ? word_at(u) : 0;
+  auto each_word = [&](auto use) {  // use(word, whether it is one of the share)
 #pragma unroll
-    for (int k = 0; k < kKeep; ++k)
-      if (u == k) w = kept[k];
-    if (u >= kKeep) w = binned[min(j0 + 64 * u + lane, n_run - 1)];
-    return w;
+    for (int u = 0; u < kKeep; ++u)
+      if (j0 + 64 * u < j1) use(kept[u], j0 + 64 * u + lane < j1);
+    if (j0 + 64 * kKeep >= j1) return;
+    uint64_t w[kAhead], next[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) next[k] = word_at(kKeep + k);
+    for (int u0 = kKeep; j0 + 64 * u0 < j1; u0 += kAhead) {
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        w[k] = next[k];
+        next[k] = word_at(u0 + kAhead + k);
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+        if (j0 + 64 * (u0 + k) < j1) use(w[k], j0 + 64 * (u0 + k) + lane < j1);
+    }
   };
-  for (int u = 0; j0 + 64 * u < j1; ++u) {
-    const Ballots s = ballots(word_of(u), j0 + 64 * u + lane < j1);
-    count += __popcll(s.of(lane16));
-  }
+  int count = 0;
+  each_word([&](uint64_t word, bool live) { count += __popcll(ballots(word, live).of(lane16)); });
   if (lane < kBinClusters) s_cnt[wave][lane] = count;
   __syncthreads();
   int sz = 0, before = 0;  // of cluster lane16, in every 16-lane row: its size; its tokens in earlier waves' shares
@@ -280,9 +292,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   }
   const int my_end = row16_incl_scan(sz), my_off = my_end - sz;  // where the cluster lies inside the run
   int next = my_off + before;
-  for (int u = 0; j0 + 64 * u < j1; ++u) {
-    const uint64_t word = word_of(u);
-    const bool live = j0 + 64 * u + lane < j1;
+  each_word([&](uint64_t word, bool live) {
     const Ballots s = ballots(word, live);
     const int v = (int)(word & (kBinClusters - 1)), t = (int)(word / kBinClusters);
     const int dest = __shfl(next, v, 16) + __popcll(s.of(v) & lanes_below());
@@ -292,7 +302,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
       else far_list[dest] = t;
       if (a.token_row) a.token_row[r0 + t] = run0 + dest;
     }
-  }
+  });
   if (tid < ncl) {
     if (a.cluster_offsets) a.cluster_offsets[c0 + cf + tid] = run0 + my_off;
     if (a.cluster_sizes) a.cluster_sizes[c0 + cf + tid] = sz;
@@ -303,15 +313,17 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   // ---- fetch, store in place, sum ----
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 kr[4], vr[4];
-  auto fetch = [&](int base, u32x4 (&kr)[4], u32x4 (&vr)[4]) {
-    int t[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)  // shares beyond the run fetch its last row again and are not stored
-      t[u] = s_list[min(min(base + 16 * u + grp, n_run - 1), kListRows - 1)];
-    if (!in_lds) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) t[u] = far_list[min(base + 16 * u + grp, n_run - 1)];
-    }
+  // Lanes u, u + 4, ... of a 16-lane row: the token of the row's u-th share of the chunk (row 16 u + grp); shares beyond
+  // the run repeat its last row and are not stored.
+  auto token_of = [&](int base) {
+    const int j = min(base + 16 * (lane16 & 3) + grp, n_run - 1);
+    int t = s_list[min(j, kListRows - 1)];
+    if (!in_lds) t = far_list[j];
+    return t;
+  };
+  auto fetch = [&](int tokens, u32x4 (&kr)[4], u32x4 (&vr)[4]) {
+    const int t[4] = {(int)dpp_mov_u32<0x00>((uint32_t)tokens), (int)dpp_mov_u32<0x55>((uint32_t)tokens),
+                      (int)dpp_mov_u32<0xAA>((uint32_t)tokens), (int)dpp_mov_u32<0xFF>((uint32_t)tokens)};  // of the quad
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int64_t at = (r0 + t[u]) * kRowBytes + lane16 * 16;
@@ -346,7 +358,11 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
     cur_end = __builtin_amdgcn_readfirstlane(__shfl(my_end, cur & 15, 16));
   };
   bounds();
-  if (n_run > 0) fetch(0, kr, vr);
+  int tokens = 0;
+  if (n_run > 0) {
+    fetch(token_of(0), kr, vr);
+    tokens = token_of(kMoveRows);
+  }
   for (int base = 0; base < n_run; base += kMoveRows) {
     const int nb = min(kMoveRows, n_run - base);
     lds_barrier();  // the previous chunk has been summed
@@ -355,6 +371,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
       *reinterpret_cast<u32x4 *>(&s_rows[16 * u + grp][lane16 * 8]) = kr[u];
       if constexpr (kMove) *reinterpret_cast<u32x4 *>(&s_rows[16 * u + grp][kHeadDim + lane16 * 8]) = vr[u];
     }
+    asm volatile("" : "+v"(tokens));  // arrived, too (loaded behind the rows): no wait for them behind the stores
     if constexpr (kMove) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {  // after the copies: a wait placed behind a store would wait for the store
@@ -366,7 +383,10 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
         }
       }
     }
-    if (base + kMoveRows < n_run) fetch(base + kMoveRows, kr, vr);  // in flight while this chunk is summed
+    if (base + kMoveRows < n_run) {  // in flight while this chunk is summed, with the tokens of the chunk after it
+      fetch(tokens, kr, vr);
+      tokens = token_of(base + 2 * kMoveRows);
+    }
     lds_barrier();
     while (cur < ncl) {
       int j = max(cur_off - base, 0);
