@@ -127,8 +127,10 @@ __global__ __launch_bounds__(kRankThreads) void build_rank_kernel(BuildArgs a) {
     if (c[u] >= 0) out[64 * u] = (uint16_t)(mine[c[u] >> 4] + rank[u]);
 }
 
-__global__ __launch_bounds__(1024) void build_scan_kernel(BuildArgs a) {
-  __shared__ int scr[1024 / 64 + 1];
+// T threads per segment: one wave where the bins of a segment fit it (2048 segments of 30 tokens: 21 -> 4.6 us).
+template <int T>
+__global__ __launch_bounds__(T) void build_scan_kernel(BuildArgs a) {
+  __shared__ int scr[T / 64 + 1];
   const int seg = blockIdx.x, tid = threadIdx.x;
   const int c0 = a.seg_cluster_ptr[seg], kc_all = a.seg_cluster_ptr[seg + 1] - c0, kc = min(kc_all, a.max_kc);
   const int n_bins = (kc + kBinClusters - 1) / kBinClusters;
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(1024) void build_scan_kernel(BuildArgs a) {
   const int blocks = (n + kBuildBlock - 1) / kBuildBlock;
   int32_t *start = a.bin_start + (size_t)seg * (a.bin_stride + 1);
   int carry = 0;
-  for (int i0 = 0; i0 < n_bins; i0 += 1024) {
+  for (int i0 = 0; i0 < n_bins; i0 += T) {
     const int i = i0 + tid;
     int run = 0;
     if (i < n_bins) {
@@ -155,13 +157,13 @@ __global__ __launch_bounds__(1024) void build_scan_kernel(BuildArgs a) {
       }
     }
     int tot;
-    const int ex = block_excl_scan<int, 1024 / 64>(run, scr, tot);
+    const int ex = block_excl_scan<int, T / 64>(run, scr, tot);
     if (i < n_bins) start[i] = carry + ex;
     carry += tot;
   }
   if (tid == 0) start[n_bins] = carry;
   // clusters beyond the host's bound received no token: they are reported empty
-  for (int i = a.max_kc + tid; i < kc_all; i += 1024) {
+  for (int i = a.max_kc + tid; i < kc_all; i += T) {
     if (a.cluster_offsets) a.cluster_offsets[c0 + i] = carry;
     if (a.cluster_sizes) a.cluster_sizes[c0 + i] = 0;
   }
@@ -470,7 +472,8 @@ hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s) {
     }
     hipLaunchKernelGGL(build_rank_kernel, dim3(L.n_blocks, p.n_seg), dim3(kRankThreads), lds, s, a);
   }
-  hipLaunchKernelGGL(build_scan_kernel, dim3(p.n_seg), dim3(1024), 0, s, a);
+  if (L.bin_stride <= 64) hipLaunchKernelGGL(build_scan_kernel<64>, dim3(p.n_seg), dim3(64), 0, s, a);
+  else hipLaunchKernelGGL(build_scan_kernel<1024>, dim3(p.n_seg), dim3(1024), 0, s, a);
   if (L.n_blocks > 0 && p.max_kc > 0)
     hipLaunchKernelGGL(build_place_kernel, dim3((p.max_rows + 255) / 256, p.n_seg), dim3(256), 0, s, a);
   if (p.max_kc > 0) {

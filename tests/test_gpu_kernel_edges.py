@@ -147,7 +147,7 @@ def _tokens(rows, clusters, spread, seed):
 
 
 @pytest.mark.parametrize("spread", ["uniform", "one_bin", "runs"])
-@pytest.mark.parametrize("clusters", [1, 16, 17, 33, 1000])
+@pytest.mark.parametrize("clusters", [1, 16, 17, 33, 1000, 1024, 1025])
 def test_build_at_block_bin_and_list_edges(clusters, spread):
     """Token blocks of 4096, waves of 64, bins of 16 clusters, runs above and below the 1024 tokens whose list stays in
     LDS, chunks of 64 rows.  Bit-exact, as in test_gpu_build."""
