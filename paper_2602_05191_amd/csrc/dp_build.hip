@@ -462,7 +462,7 @@ hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s) {
   a.bin_stride = L.bin_stride;
   a.max_kc = p.max_kc;
   a.max_rows = p.max_rows;
-  if (L.n_blocks > 0 && L.bin_stride > 0) {
+  if (L.n_blocks > 0 && (L.bin_stride > 0 || p.token_row)) {  // (no cluster at all: every token is left out)
     // a count per wave and bin lives in LDS: 2 bytes per cluster of the longest segment (128 KB at the 65536 limit)
     const size_t lds = (size_t)kRankWaves * L.bin_stride * sizeof(uint16_t);
     if (lds > 32768) {

@@ -157,6 +157,13 @@ def test_build_at_block_bin_and_list_edges(clusters, spread):
     check_build(t, gpu_build(t), oracle.build_cluster_cache(t))
 
 
+def test_build_without_any_cluster_leaves_every_token_out():
+    from test_gpu_build import gpu_build
+    t = _tokens([5, 4097], [1, 1], "uniform", seed=79)
+    t.seg_cluster_ptr[:] = 0
+    assert (gpu_build(t)["token_row"] == -1).all()
+
+
 @pytest.mark.parametrize("clusters", [2, 17])
 def test_kmeans_update_on_long_clusters(clusters):
     """The keys-only move (two halves of a workgroup take the clusters in turn) over runs of 64 to 9000 rows: after
