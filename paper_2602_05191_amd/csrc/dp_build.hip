@@ -52,7 +52,7 @@ struct BuildArgs {
   float *v_sums;                                         // nullable
   int32_t *hist;                                         // [n_seg, n_blocks, bin_stride]
   uint16_t *rank;                                        // [n_seg, n_blocks * kBuildBlock]
-  int32_t *bin_start;                                    // [n_seg, bin_stride + 1]
+  int32_t *bin_start;                                    // [n_seg, bin_stride + 1] (there is none if max_rows is 0)
   uint64_t *binned;                                      // [n_seg, max_rows]: 16 x token + cluster of the bin
   int32_t *row_token;                                    // [n_seg, max_rows]: token of each row, for runs too long for LDS
   int32_t n_blocks, bin_stride, max_kc, max_rows;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(T) void build_scan_kernel(BuildArgs a) {
   const int blocks = (n + kBuildBlock - 1) / kBuildBlock;
   int32_t *start = a.bin_start + (size_t)seg * (a.bin_stride + 1);
   int carry = 0;
-  for (int i0 = 0; i0 < n_bins; i0 += T) {
+  for (int i0 = 0; i0 < (a.max_rows > 0 ? n_bins : 0); i0 += T) {
     const int i = i0 + tid;
     int run = 0;
     if (i < n_bins) {
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(T) void build_scan_kernel(BuildArgs a) {
     if (i < n_bins) start[i] = carry + ex;
     carry += tot;
   }
-  if (tid == 0) start[n_bins] = carry;
+  if (tid == 0 && a.max_rows > 0) start[n_bins] = carry;
   // clusters beyond the host's bound received no token: they are reported empty
   for (int i = a.max_kc + tid; i < kc_all; i += T) {
     if (a.cluster_offsets) a.cluster_offsets[c0 + i] = carry;
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   const int ncl = min(kBinClusters, kc - cf);
   const int lane16 = tid & 15, grp = tid >> 4;
   const int32_t *start = a.bin_start + (size_t)seg * (a.bin_stride + 1) + bin;
-  const int run0 = start[0], n_run = start[1] - run0;
+  const int run0 = a.max_rows > 0 ? start[0] : 0, n_run = a.max_rows > 0 ? start[1] - run0 : 0;
   const uint64_t *binned = a.binned + (size_t)seg * a.max_rows + run0;
   int32_t *far_list = a.row_token + (size_t)seg * a.max_rows + run0;
   const bool in_lds = n_run <= kListRows;
@@ -432,7 +432,10 @@ BuildLayout layout_of(int n_seg, int max_rows, int max_kc) {
 
 }  // namespace
 
-size_t build_workspace_bytes(int n_seg, int max_rows, int max_kc) { return layout_of(n_seg, max_rows, max_kc).total; }
+// (without rows nothing is sorted: no workspace)
+size_t build_workspace_bytes(int n_seg, int max_rows, int max_kc) {
+  return max_rows > 0 ? layout_of(n_seg, max_rows, max_kc).total : 0;
+}
 
 hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s) {
   if (p.n_seg == 0) return hipSuccess;

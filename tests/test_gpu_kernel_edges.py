@@ -164,6 +164,23 @@ def test_build_without_any_cluster_leaves_every_token_out():
     assert (gpu_build(t)["token_row"] == -1).all()
 
 
+def test_build_without_any_row_needs_no_workspace():
+    import torch
+    import paper_2602_05191_amd as dp
+    dev = lambda *a, **k: torch.full(*a, device="cuda", **k)
+    k = dev((1, 128), 0x7FC0, dtype=torch.int16)
+    ptr = torch.tensor([0, 3, 40], dtype=torch.int32, device="cuda")
+    pf = dp.Prefill(k, k, dev((1,), 0, dtype=torch.int32), dev((2,), 0, dtype=torch.int64),
+                    dev((2,), 0, dtype=torch.int32), ptr, 40, 37, 0)
+    assert dp.dp_build_workspace_bytes(pf) == 0
+    off, size = (dev((40,), -7, dtype=torch.int32) for _ in range(2))
+    kc, vc = (dev((40, 128), 0x7FC0, dtype=torch.int16) for _ in range(2))
+    dp.dp_build_cluster_cache(pf, k.clone(), k.clone(), off, size, kc, vc, torch.empty(0, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    for out in (off, size, kc, vc):
+        assert (out == 0).all()
+
+
 @pytest.mark.parametrize("clusters", [2, 17])
 def test_kmeans_update_on_long_clusters(clusters):
     """The keys-only move (two halves of a workgroup take the clusters in turn) over runs of 64 to 9000 rows: after
