@@ -206,10 +206,10 @@ __device__ __forceinline__ uint32_t f64_to_bf16_rne(double x) {
 // place; the next chunk's rows are fetched while the chunk is summed.  Thread d sums column d (key dimensions, then
 // value dimensions) of the chunk's rows in row order, in fp64, and writes a cluster's means when its last row has gone
 // by.  A sum carries over from chunk to chunk.
-// One long run is one workgroup's serial work (a cluster of 131072 of 1 M tokens: 2048 chunks of 2.2 us), so nothing in it
+// One long run is one workgroup's serial work (a cluster of 131072 tokens: 2048 chunks of 2.4 us), so nothing in it
 // may wait in turn: the list is read in batches, one ahead, the tokens of a chunk come a chunk before its rows and the
-// rows a chunk before they are summed (all tokens of 8 segments in one cluster each: 6311 -> 4610 us; half of them 3812 ->
-// 2827; with the list read in front of every chunk's rows these were slower than the one-level sort: 5330, 2850).
+// rows a chunk before they are summed (all tokens of 8 segments in one cluster each: 6311 -> 5025 us; half of them 3812 ->
+// 2659; with the list read in front of every chunk's rows these were slower than the one-level sort: 5390, 2860).
 // Rows go by once: non-temporal loads and stores (move of 8 x 131072 tokens 228 -> 215 us = 5.2 TB/s over 1.11 GB; a
 // plain copy of 2 GB runs at 4.7 TB/s on the same card).
 // kMove = false: keys only (the update step of k-means): nothing is stored in place, no value is read, the two halves
@@ -320,6 +320,8 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   auto token_of = [&](int base) {
     const int j = min(base + 16 * (lane16 & 3) + grp, n_run - 1);
     int t = s_list[min(j, kListRows - 1)];
+    // (two loads: merged into one through a flat address they would be waited for at the next LDS barrier)
+    asm volatile("" : "+v"(t));
     if (!in_lds) t = far_list[j];
     return t;
   };
