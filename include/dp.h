@@ -284,8 +284,9 @@ typedef struct {
 } dp_prefill;
 
 /* Host-only.  Device workspace dp_build_cluster_cache needs (per segment and
- * 4096-token block one int32 per 16 clusters, plus 14 bytes per token); 0 for an
- * invalid description. */
+ * 4096-token block one int32 per 16 clusters, plus 8 bytes per token of the
+ * longest segment, 12 from 2^28 tokens on); 0 for an invalid description and
+ * where there are no rows. */
 size_t dp_build_workspace_bytes(const dp_prefill *in);
 
 /* Builds what the decode entry points read (the dp_problem fields of the same

@@ -51,9 +51,9 @@ struct BuildArgs {
   int32_t *cluster_offsets, *cluster_sizes, *token_row;  // all nullable
   float *v_sums;                                         // nullable
   int32_t *hist;                                         // [n_seg, n_blocks, bin_stride]
-  uint16_t *rank;                                        // [n_seg, n_blocks * kBuildBlock]
+  uint16_t *rank;                                        // [n_seg, max_rows], in the place of row_token until the move
   int32_t *bin_start;                                    // [n_seg, bin_stride + 1] (there is none if max_rows is 0)
-  uint64_t *binned;                                      // [n_seg, max_rows]: 16 x token + cluster of the bin
+  void *binned;                                          // [n_seg, max_rows]: 16 x token + cluster of the bin
   int32_t *row_token;                                    // [n_seg, max_rows]: token of each row, for runs too long for LDS
   int32_t n_blocks, bin_stride, max_kc, max_rows;
 };
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kRankThreads) void build_rank_kernel(BuildArgs a) {
     row[i] = run;
   }
   __syncthreads();
-  uint16_t *out = a.rank + ((size_t)seg * a.n_blocks + blk) * kBuildBlock + wave * (64 * kRankRounds) + lane_id();
+  uint16_t *out = a.rank + (size_t)seg * a.max_rows + t0;
 #pragma unroll
   for (int u = 0; u < kRankRounds; ++u)
     if (c[u] >= 0) out[64 * u] = (uint16_t)(mine[c[u] >> 4] + rank[u]);
@@ -169,6 +169,10 @@ __global__ __launch_bounds__(T) void build_scan_kernel(BuildArgs a) {
   }
 }
 
+// The word of a token in its bin is 16 x token + cluster: 32 bits hold it for segments of less than kShortRows tokens.
+constexpr int kShortRows = 1 << 28;
+
+template <class Word>
 __global__ __launch_bounds__(256) void build_place_kernel(BuildArgs a) {
   const int seg = blockIdx.y;
   const int n = min(a.seg_rows[seg], a.max_rows);
@@ -176,12 +180,12 @@ __global__ __launch_bounds__(256) void build_place_kernel(BuildArgs a) {
   if (t >= n) return;
   const int c0 = a.seg_cluster_ptr[seg], kc = min(a.seg_cluster_ptr[seg + 1] - c0, a.max_kc);
   const int c = a.assignment[a.seg_row_base[seg] + t];
-  const int rank = a.rank[(size_t)seg * a.n_blocks * kBuildBlock + t];  // (undefined for a token that is left out)
+  const int rank = a.rank[(size_t)seg * a.max_rows + t];  // (undefined for a token that is left out)
   if ((unsigned)c >= (unsigned)kc) return;
   const int bin = c / kBinClusters;
   const int at = a.bin_start[(size_t)seg * (a.bin_stride + 1) + bin] +
                  a.hist[((size_t)seg * a.n_blocks + t / kBuildBlock) * a.bin_stride + bin] + rank;
-  a.binned[(size_t)seg * a.max_rows + at] = (uint64_t)t * kBinClusters + (uint64_t)(c % kBinClusters);
+  static_cast<Word *>(a.binned)[(size_t)seg * a.max_rows + at] = (Word)t * kBinClusters + (Word)(c % kBinClusters);
 }
 
 // double -> bf16 bits with ONE rounding to 8 significant bits, ties to even.  Values whose magnitude
@@ -217,7 +221,7 @@ __device__ __forceinline__ uint32_t f64_to_bf16_rne(double x) {
 constexpr int kMoveRows = 64;
 constexpr int kListRows = 1024;  // longest run whose list stays in LDS
 
-template <bool kMove>
+template <bool kMove, class Word>
 __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   constexpr int kCols = kMove ? 2 * kHeadDim : kHeadDim;
   __shared__ __align__(16) uint16_t s_rows[kMoveRows][kCols];  // key | value of every row of the chunk
@@ -232,7 +236,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   const int lane16 = tid & 15, grp = tid >> 4;
   const int32_t *start = a.bin_start + (size_t)seg * (a.bin_stride + 1) + bin;
   const int run0 = a.max_rows > 0 ? start[0] : 0, n_run = a.max_rows > 0 ? start[1] - run0 : 0;
-  const uint64_t *binned = a.binned + (size_t)seg * a.max_rows + run0;
+  const Word *binned = static_cast<const Word *>(a.binned) + (size_t)seg * a.max_rows + run0;
   int32_t *far_list = a.row_token + (size_t)seg * a.max_rows + run0;
   const bool in_lds = n_run <= kListRows;
 
@@ -248,7 +252,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
       return m;
     }
   };
-  auto ballots = [&](uint64_t word, bool live) {
+  auto ballots = [&](Word word, bool live) {
     Ballots s;
     s.live = __ballot(live);
 #pragma unroll
@@ -258,7 +262,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   // The wave's share, 64 words at a time: the first kKeep of a lane stay in registers from the first pass to the second,
   // the others are loaded kAhead at a time, one batch ahead.
   constexpr int kKeep = 2, kAhead = 8;
-  uint64_t kept[kKeep];
+  Word kept[kKeep];
   auto word_at = [&](int u) { return binned[min(j0 + 64 * u + lane, n_run - 1)]; };
 #pragma unroll
   for (int u = 0; u < kKeep; ++u) kept[u] = n_run > 0 ? word_at(u) : 0;
@@ -267,7 +271,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
     for (int u = 0; u < kKeep; ++u)
       if (j0 + 64 * u < j1) use(kept[u], j0 + 64 * u + lane < j1);
     if (j0 + 64 * kKeep >= j1) return;
-    uint64_t w[kAhead], next[kAhead];
+    Word w[kAhead], next[kAhead];
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) next[k] = word_at(kKeep + k);
     for (int u0 = kKeep; j0 + 64 * u0 < j1; u0 += kAhead) {
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
     }
   };
   int count = 0;
-  each_word([&](uint64_t word, bool live) { count += __popcll(ballots(word, live).of(lane16)); });
+  each_word([&](Word word, bool live) { count += __popcll(ballots(word, live).of(lane16)); });
   if (lane < kBinClusters) s_cnt[wave][lane] = count;
   __syncthreads();
   int sz = 0, before = 0;  // of cluster lane16, in every 16-lane row: its size; its tokens in earlier waves' shares
@@ -294,7 +298,7 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
   }
   const int my_end = row16_incl_scan(sz), my_off = my_end - sz;  // where the cluster lies inside the run
   int next = my_off + before;
-  each_word([&](uint64_t word, bool live) {
+  each_word([&](Word word, bool live) {
     const Ballots s = ballots(word, live);
     const int v = (int)(word & (kBinClusters - 1)), t = (int)(word / kBinClusters);
     const int dest = __shfl(next, v, 16) + __popcll(s.of(v) & lanes_below());
@@ -415,21 +419,31 @@ __global__ __launch_bounds__(256) void build_move_kernel(BuildArgs a) {
 }
 
 struct BuildLayout {
-  size_t hist, rank, bin_start, binned, row_token, total;  // byte offsets
+  size_t hist, row_token, bin_start, binned, total;  // byte offsets
   int n_blocks, bin_stride;
 };
 BuildLayout layout_of(int n_seg, int max_rows, int max_kc) {
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  const size_t rows = (size_t)n_seg * max_rows, word = max_rows < kShortRows ? sizeof(uint32_t) : sizeof(uint64_t);
   BuildLayout L;
   L.n_blocks = (int)(((int64_t)max_rows + kBuildBlock - 1) / kBuildBlock);
   L.bin_stride = ((max_kc + kBinClusters - 1) / kBinClusters + 1) / 2 * 2;  // even: the tables are cleared word by word
   L.hist = 0;
-  L.rank = up((size_t)n_seg * L.n_blocks * L.bin_stride * sizeof(int32_t));
-  L.bin_start = L.rank + up((size_t)n_seg * L.n_blocks * kBuildBlock * sizeof(uint16_t));
+  L.row_token = up((size_t)n_seg * L.n_blocks * L.bin_stride * sizeof(int32_t));
+  L.bin_start = L.row_token + up(rows * sizeof(int32_t));  // (the ranks lie where row_token comes: half of it)
   L.binned = L.bin_start + up((size_t)n_seg * (L.bin_stride + 1) * sizeof(int32_t));
-  L.row_token = L.binned + up((size_t)n_seg * max_rows * sizeof(uint64_t));
-  L.total = L.row_token + up((size_t)n_seg * max_rows * sizeof(int32_t));
+  L.total = L.binned + up(rows * word);
   return L;
+}
+
+template <class Word>
+void place_and_move(const BuildArgs &a, int n_seg, hipStream_t s) {
+  if (a.max_kc == 0) return;
+  if (a.max_rows > 0)
+    hipLaunchKernelGGL(build_place_kernel<Word>, dim3(((unsigned)a.max_rows + 255) / 256, n_seg), dim3(256), 0, s, a);
+  const dim3 grid((a.max_kc + kBinClusters - 1) / kBinClusters, n_seg);
+  if (a.k_cache) hipLaunchKernelGGL((build_move_kernel<true, Word>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((build_move_kernel<false, Word>), grid, dim3(256), 0, s, a);
 }
 
 }  // namespace
@@ -459,9 +473,9 @@ hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s) {
   a.token_row = p.token_row;
   a.v_sums = p.v_sums;
   a.hist = reinterpret_cast<int32_t *>(ws + L.hist);
-  a.rank = reinterpret_cast<uint16_t *>(ws + L.rank);
+  a.rank = reinterpret_cast<uint16_t *>(ws + L.row_token);
   a.bin_start = reinterpret_cast<int32_t *>(ws + L.bin_start);
-  a.binned = reinterpret_cast<uint64_t *>(ws + L.binned);
+  a.binned = ws + L.binned;
   a.row_token = reinterpret_cast<int32_t *>(ws + L.row_token);
   a.n_blocks = L.n_blocks;
   a.bin_stride = L.bin_stride;
@@ -479,13 +493,8 @@ hipError_t launch_build(const BuildProblem &p, void *workspace, hipStream_t s) {
   }
   if (L.bin_stride <= 64) hipLaunchKernelGGL(build_scan_kernel<64>, dim3(p.n_seg), dim3(64), 0, s, a);
   else hipLaunchKernelGGL(build_scan_kernel<1024>, dim3(p.n_seg), dim3(1024), 0, s, a);
-  if (L.n_blocks > 0 && p.max_kc > 0)
-    hipLaunchKernelGGL(build_place_kernel, dim3((p.max_rows + 255) / 256, p.n_seg), dim3(256), 0, s, a);
-  if (p.max_kc > 0) {
-    const dim3 grid((p.max_kc + kBinClusters - 1) / kBinClusters, p.n_seg);
-    if (p.k_cache) hipLaunchKernelGGL(build_move_kernel<true>, grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(build_move_kernel<false>, grid, dim3(256), 0, s, a);
-  }
+  if (p.max_rows < kShortRows) place_and_move<uint32_t>(a, p.n_seg, s);
+  else place_and_move<uint64_t>(a, p.n_seg, s);
   return hipGetLastError();
 }
 

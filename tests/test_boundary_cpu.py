@@ -95,3 +95,16 @@ def test_product_package_does_not_import_the_oracle():
             if f.endswith((".py", ".hip", ".hpp", ".h")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.lower(), f"{f} mentions the oracle"
+
+
+@pytest.mark.parametrize("rows, clusters", [(1, 1), (30, 4), (1500, 16), (5003, 312), (131072, 16), (131072, 8192)])
+def test_build_workspace_is_what_the_header_says(lib, rows, clusters):
+    from paper_2602_05191_amd.binding import _Prefill
+    n_seg = 3
+    p = _Prefill(n_seg=n_seg, head_dim=128, total_clusters=n_seg * clusters, max_clusters_per_seg=clusters,
+                 max_rows_per_seg=rows)
+    blocks, bins = -(-rows // 4096), -(-clusters // 16)
+    # 8 bytes per token, one int32 per 4096-token block and bin (an even number of bins), one per bin and segment;
+    # four parts, each rounded up to 256 bytes
+    most = n_seg * (8 * rows + 4 * (blocks + 1) * (bins + 2)) + 4 * 256
+    assert 8 * n_seg * rows <= lib.dp_build_workspace_bytes(C.byref(p)) <= most

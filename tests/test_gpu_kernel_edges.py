@@ -164,6 +164,29 @@ def test_build_without_any_cluster_leaves_every_token_out():
     assert (gpu_build(t)["token_row"] == -1).all()
 
 
+def test_build_with_words_of_64_bits():
+    """A bound of 2^28 rows per segment: the sort's words take 64 bits.  Same outputs as with the exact bound."""
+    import torch
+    import paper_2602_05191_amd as dp
+    t = _tokens([5000], [100], "one_bin", seed=81)
+    up = lambda a, dt: torch.from_numpy(np.ascontiguousarray(a).view(dt)).cuda()
+    out = []
+    for bound in (5000, 1 << 28):
+        pf = dp.Prefill(up(t.k_tokens, np.int16), up(t.v_tokens, np.int16), up(t.assignment, np.int32),
+                        up(t.seg_row_base, np.int64), up(t.seg_rows, np.int32), up(t.seg_cluster_ptr, np.int32),
+                        100, 100, bound)
+        bufs = [torch.full(s, -7, dtype=d, device="cuda") for s, d in
+                (((5000, 128), torch.int16), ((5000, 128), torch.int16), ((100,), torch.int32), ((100,), torch.int32),
+                 ((100, 128), torch.int16), ((100, 128), torch.int16))]
+        row = torch.full((5000,), -7, dtype=torch.int32, device="cuda")
+        ws = torch.empty(dp.dp_build_workspace_bytes(pf), dtype=torch.uint8, device="cuda")
+        dp.dp_build_cluster_cache(pf, *bufs, ws, token_row=row)
+        torch.cuda.synchronize()
+        out.append(bufs + [row])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
 def test_build_without_any_row_needs_no_workspace():
     import torch
     import paper_2602_05191_amd as dp
