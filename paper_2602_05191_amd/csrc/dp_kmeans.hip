@@ -344,19 +344,25 @@ hipError_t launch_kmeans_assign(const KmeansProblem &p, float *half_norm, hipStr
   a.total_clusters = p.total_clusters;
   if (p.total_clusters > 0)
     hipLaunchKernelGGL(km_norm_kernel, dim3((p.total_clusters + 15) / 16), dim3(256), 0, s, a);
-  // Tokens per workgroup.  128 per wave need the fewest operand bytes per product and the fewest instructions per score
-  // (8 x 131072 tokens x 8192 centroids: 1450 us against 1820 with 64 per wave), but end with 14 us in which every
-  // token's last four candidates are scored again: worth it from about 1250 centroids on (32768 tokens x 2048: 126
-  // against 137 us; 64 segments x 16384 x 512: 202 against 152) and where the launch fills the chip at its two
-  // workgroups per CU (24576 x 1536, 384 workgroups: 96 against 81).  Below that 32 per wave while these fit one round
-  // at three workgroups per CU (8 x 12000 tokens: 33.2 against 35.4 us; 8192 tokens, one segment: 13.2 against 17.5),
-  // then 64 (8 x 16384: 46 against 52; 64 x 4096: 22 against 25).
+  // Tokens per workgroup.  128 per wave need the fewest operand bytes per product and the fewest instructions per score,
+  // but end with 14 us in which every token's last four candidates are scored again.  Against 64 per wave, where the
+  // launch fills the chip at its two workgroups per CU (us):
+  //   centroids             1024       1280       1536       1792       2048       4096
+  //   8 x 32768 tokens     79 / 72    88 / 87    99 / 102  111 / 117  121 / 132  211 / 252
+  //   8 x 65536           143 / 130  162 / 160  182 / 188  203 / 217  223 / 245  398 / 475
+  //   8 x 131072          260 / 250  299 / 306  341 / 364  382 / 419  426 / 477  773 / 928
+  // and where it does not (8 x 24576, 384 workgroups) they lose up to 4096 (192 / 191).  Below that 32 per wave while these
+  // fit one round at three workgroups per CU (8 x 12000 tokens: 33.2 against 35.4 us; 8192 tokens, one segment: 13.2
+  // against 17.5), then 64 (8 x 16384: 46 against 52; 64 x 4096: 22 against 25).
+  // The host sees the mean of the centroids and the longest segment only: workgroups past the end of a shorter segment
+  // leave at once, but count here (one segment of 131072 x 8192 among 31 of 1000 x 64 takes 64 per wave, 260 us, where 128
+  // would take 226; four of 40000 x 2500 among 28 of 3000 x 200: 120, and 131 with 128).
   auto grid = [&](int tm) {
     const int per_block = 16 * tm * (kKmThreads / 64);
     return dim3((p.max_rows + per_block - 1) / per_block, p.n_seg);
   };
   auto blocks = [&](int tm) { return (int64_t)grid(tm).x * grid(tm).y; };
-  if (p.total_clusters / p.n_seg >= 2048 && blocks(8) >= 2 * kKmCus)
+  if (p.total_clusters / p.n_seg >= 1536 && blocks(8) >= 2 * kKmCus)
     hipLaunchKernelGGL(km_assign8_kernel, grid(8), dim3(kKmThreads), 0, s, a);
   else if (blocks(2) <= 3 * kKmCus)
     hipLaunchKernelGGL(km_assign2_kernel, grid(2), dim3(kKmThreads), 0, s, a);

@@ -217,10 +217,10 @@ def test_kmeans_update_on_long_clusters(clusters):
     assert np.array_equal(got_a, ref_a) and np.array_equal(got_c, ref_c)
 
 
-@pytest.mark.parametrize("last", [6010, 60])
+@pytest.mark.parametrize("last", [6010, 1908, 1907, 60])
 def test_kmeans_assign_same_bits_whatever_the_launch(last):
-    """Eight segments together take 128 tokens per wave (2048 centroids per segment on average) or 64 (fewer); one
-    alone takes 32.  The same products are summed in the same order: index and score are equal to the bit, at token
+    """Eight segments together take 128 tokens per wave (2048 or 1536 centroids per segment on average) or 64 (fewer);
+    one alone takes 32.  The same products are summed in the same order: index and score are equal to the bit, at token
     and centroid counts around the tiles, for equal centroids in one quad and far apart, and with NaN and inf."""
     import torch
     import paper_2602_05191_amd as dp
