@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n_q_heads", [1, 5, 16, 20])
 def test_dense_decode_at_tile_and_split_edges(n_q_heads):
-    """16-row tiles, 64-row steps of a workgroup, 256-row splits, and passes of 16 heads."""
+    """16-row tiles, 64-row chunks (here one per workgroup), and passes of 16 heads."""
     ctx = [1, 15, 16, 17, 63, 64, 65, 255, 256, 257, 511, 513, 1100]
     c = make_cache(batch=len(ctx), n_kv_heads=1, n_q_heads=n_q_heads, context=ctx, mean_cluster=16, q_scale=0.7, seed=61)
     out, lse = H.gpu_dense_decode(c, H.segment_rows(c))
@@ -122,6 +122,18 @@ def test_dense_decode_long_sums_keep_fp32_precision(seed):
     # 37 tiles give 1.8e-7, one chain over 592 rows 5.9e-7.  Scores of rms 3 (base 2), off by 6e-8 and rounded twice,
     # add 2.5e-7: together 3.1e-7 against 6.4e-7.
     assert rel <= 4.2e-7, rel
+
+
+@pytest.mark.parametrize("n", [40001, 40017])
+@pytest.mark.parametrize("n_q_heads", [5, 20])
+def test_dense_decode_shares_of_several_chunks(n, n_q_heads):
+    """One segment with more chunks than partial slots: shares of three chunks, so a wave has several tiles, in passes of
+    5, 16 and 4 heads; scores grow along the rows, so the maximum moves in late tiles."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=n_q_heads, context=n, mean_cluster=64, size_hi=256, q_scale=0.3,
+                   seed=68)
+    c.q[..., 0] = BF16["one"]
+    c.k_cache[:, 0] = np.linspace(-60, 60, n).astype(np.float32).view(np.uint32) >> 16
+    _dense_against_oracle(c)
 
 
 def _tokens(rows, clusters, spread, seed):
