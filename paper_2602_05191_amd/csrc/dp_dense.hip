@@ -3,9 +3,8 @@
 // measured against (Sec. 5.3).
 //
 // HBM-bound streaming kernel (512 B per token).  The K and V rows of a segment are
-// contiguous, so a workgroup streams a row range [split * c, split * c + c) once and
-// scores each row against up to 16 query heads of the GQA group at once: the cache
-// is read once per KV head.  Both contractions run on the matrix cores, and the
+// contiguous, so a workgroup streams a range of rows once and scores each row against
+// up to 16 query heads of the GQA group at once: the cache is read once per KV head.  Both contractions run on the matrix cores, and the
 // operands go from global memory straight into the instructions' register layouts,
 // with nothing exchanged between lanes and nothing staged in LDS:
 //   scores  S[16 rows x 16 heads] = K Q^T, four v_mfma_f32_16x16x32_bf16.  Lane l
@@ -33,10 +32,13 @@
 // keep the range below 2^-126 (exp2f, not the bare instruction, which flushes it: a value of 1e38 there still counts).
 // Matrix-core time per 16 rows: 4 x 16 + 32 x 32 cycles, whatever the group size is:
 // 29 us at 2.4 GHz for the million rows of 8 x 131072 tokens, behind 87 us of HBM
-// time at 6.2 TB/s.  Measured there at G = 4: 82 us = 6.5 TB/s with non-temporal
-// loads, 94.5 us = 5.7 TB/s with plain ones (108 us with the dot products, G softmaxes
-// per row in 16 lanes each and G x 128 multiply-adds per row on the vector ALU; that form
-// was vector-bound at G = 8).
+// time at 6.2 TB/s.  Measured there at G = 4: 81 us = 6.6 TB/s (87 us = 6.1 TB/s over
+// buffers in turn that no cache holds a part of); with plain loads 95 (111 us with the dot
+// products, G softmaxes per row in 16 lanes each and G x 128 multiply-adds per row on the
+// vector ALU; that form was vector-bound at G = 8).  Calls of one to two thousand rows per
+// segment at G = 1 are 10 to 20 % slower than that form was where the rows come from the
+// caches (8 x 1024 tokens x 8 KV heads 13.5 against 10.7 us), not where they come from HBM
+// (14.2 against 13.6; 32 x 2048 ragged 37.5 against 40.2).
 // Work split: the segments' rows, in chunks of 64, are dealt out evenly to one round of resident workgroups, whatever
 // the lengths of the segments (the lengths are on the device: every wave derives its share from them).  A share may end
 // one segment and begin the next (three segments of 24 to 45 k tokens x 8 KV heads, G = 8: 83 -> 73.5 us against equal

@@ -27,8 +27,9 @@
 // A tile's tokens are taken in two halves: the MFMAs of one run while the results of the other are looked at, in an
 // order given to the scheduler, so that a wave alone keeps both units busy (two waves in step would wait for the same
 // unit).  No load may be pending when the loop begins (below).
-// 8 x 131072 tokens x 8192 centroids: 1860 -> 1450 us = 1.52 PFLOP/s; matrix cores busy 71 % of the cycles, at the
-// 1.9 GHz the card runs at under this load.  Tried and worse: the position inside the quad as lane masks in scalar
+// 8 x 131072 tokens x 8192 centroids: 1860 -> 1450 us = 1.52 PFLOP/s in the rounds of a fit; matrix cores busy 71 % of the
+// cycles, at the 1.9 GHz the card runs at under this load.  (bench.py's line, five calls on keys of its own, reads 1545 to
+// 1565 us = 1.41 PFLOP/s: so does the kernel's own time there.)  Tried and worse: the position inside the quad as lane masks in scalar
 // registers (1660: ten scalar instructions per quad), a pair instead of a quad scored again (1510), the index itself
 // at 128 tokens per wave (1705).
 #include "dp_device.hpp"

@@ -51,7 +51,9 @@ def test_dense_decode_of_many_segments(n_seg, lengths):
     if n_seg > 4000:   # (few long ones)
         ctx = [n if n < 1000 or i % 97 == 0 else 3 for i, n in enumerate(ctx)]
     ctx[-1] = max(lengths)
-    c = make_cache(batch=n_seg, n_kv_heads=1, n_q_heads=2, context=ctx, mean_cluster=64, size_hi=256, q_scale=0.7, seed=67)
+    heads = 20 if n_seg < 10 else 2   # (two passes over a group of 20)
+    c = make_cache(batch=n_seg, n_kv_heads=1, n_q_heads=heads, context=ctx, mean_cluster=64, size_hi=256, q_scale=0.7,
+                   seed=67)
     rows = H.segment_rows(c)
     rows[rng.choice(n_seg - 1, n_seg // 8, replace=False)] = 0
     out, lse = H.gpu_dense_decode(c, rows)
