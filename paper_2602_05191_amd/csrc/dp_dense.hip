@@ -35,10 +35,11 @@
 // time at 6.2 TB/s.  Measured there at G = 4: 81 us = 6.6 TB/s (87 us = 6.1 TB/s over
 // buffers in turn that no cache holds a part of); with plain loads 95 (111 us with the dot
 // products, G softmaxes per row in 16 lanes each and G x 128 multiply-adds per row on the
-// vector ALU; that form was vector-bound at G = 8).  Calls of one to two thousand rows per
-// segment at G = 1 are 10 to 20 % slower than that form was where the rows come from the
-// caches (8 x 1024 tokens x 8 KV heads 13.5 against 10.7 us), not where they come from HBM
-// (14.2 against 13.6; 32 x 2048 ragged 37.5 against 40.2).
+// vector ALU; that form was vector-bound at G = 8).  Calls of one to five thousand rows per
+// segment at G = 1 are up to 15 % (one of 5003 x 8: 20 %) slower than that form was where the
+// rows come from the caches (40 x 1024 tokens x 8 KV heads 34.2 against 30.1 us, 8 x 2048
+// 17.1 / 16.8), not where they come from HBM (8 x 1024 12.5 / 13.7, 5003 x 8 14.6 / 14.6;
+// 2400 segments of 64 rows 23.0 / 21.4).
 // Work split: the segments' rows, in chunks of 64, are dealt out evenly to one round of resident workgroups, whatever
 // the lengths of the segments (the lengths are on the device: every wave derives its share from them).  A share may end
 // one segment and begin the next (three segments of 24 to 45 k tokens x 8 KV heads, G = 8: 83 -> 73.5 us against equal
@@ -466,10 +467,11 @@ hipError_t launch_dense(const CacheView &c, const int32_t *seg_rows, float *part
     }
   }
   if (a.whole) return hipGetLastError();
-  // From 512 heads on a head has at most 32 partial slots, four rounds of loads for one group of threads, and the heads
-  // fill the chip.  One group against eight: 512 heads (16 x 2048 tokens) 29.5 against 31.5 us for the call, 1024 heads
-  // 47.9 / 52.4, 4096 heads (64 x 1024) 54.9 / 74.0.  (Few heads with many slots: at the kernel.)
-  if (nh >= 512)
+  // A head with at most 32 pieces (as many chunks, or partial slots, which is so from 512 heads on) is merged by one group
+  // of threads in four rounds of loads.  One group against eight: 512 heads (16 x 2048 tokens) 29.5 against 31.5 us for the
+  // call, 4096 heads (64 x 1024) 54.9 / 74.0; 8 x 1024 tokens x 8 KV heads, G = 1: 11.8 / 13.5, 2048 x 8, G = 4: 10.9 / 11.6.
+  // (Few heads with many pieces: at the kernel.)
+  if (nh >= 512 || max_chunks <= 32)
     hipLaunchKernelGGL(dense_merge_kernel<1>, dim3(nh), dim3(kHeadDim), 0, s, a);
   else
     hipLaunchKernelGGL(dense_merge_kernel<8>, dim3(nh), dim3(8 * kHeadDim), 0, s, a);
