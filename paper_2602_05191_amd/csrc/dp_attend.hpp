@@ -117,6 +117,96 @@ __device__ __forceinline__ void attend_rows(RowState &st, const uint4 &qv, float
   }
 }
 
+// ---- rows of one unit of the split decode, one row per lane ----
+// A wave attends a unit of 16, 32 or 64 consecutive rows of a head's list.  Lane 16 g + j holds what row j of group g
+// needs: where its K and V rows lie and what its additive weight is the log2 of.  The row loop then fetches these with DPP
+// row broadcasts: no list is walked and nothing is looked up between the loads of successive rows.
+struct UnitRows {
+  uint32_t klo, khi, vlo, vhi;
+  int size;    // of the row's cluster, still on its way from memory; counts for an approximated one
+  int weight;  // 1: a token; 0: no row; -1: `size`
+};
+
+// lane N of every 16-lane row, in all lanes of that row
+template <int N>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, true);  // row_newbcast:N
+}
+
+// lane (i + N) % 16 of every 16-lane row, in lane i
+template <int N>
+__device__ __forceinline__ uint32_t row_rotate(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + 16 - N, 0xf, 0xf, true);  // row_ror:16-N
+}
+
+template <int N, int B>
+__device__ __forceinline__ void load_unit_rows(const UnitRows &r, int lane16, uint4 (&k)[B], uint4 (&v)[B]) {
+  if constexpr (N < B) {
+    // (an address made of two words has no address space of its own, and a flat load waits for LDS operations too)
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef const u32x4 __attribute__((address_space(1))) *global_u32x4;
+    const uint64_t ka = ((uint64_t)row_bcast<N>(r.khi) << 32 | row_bcast<N>(r.klo)) + lane16 * 16;
+    const uint64_t va = ((uint64_t)row_bcast<N>(r.vhi) << 32 | row_bcast<N>(r.vlo)) + lane16 * 16;
+    k[N] = __builtin_bit_cast(uint4, *(global_u32x4)ka);
+    v[N] = __builtin_bit_cast(uint4, *(global_u32x4)va);
+    load_unit_rows<N + 1, B>(r, lane16, k, v);
+  }
+}
+template <int N, int B>
+__device__ __forceinline__ void spread_weights(float mine, float (&w)[B]) {
+  if constexpr (N < B) {
+    w[N] = __uint_as_float(row_bcast<N>(__float_as_uint(mine)));
+    spread_weights<N + 1, B>(mine, w);
+  }
+}
+
+// batches of B rows per group, one after the other
+template <int B>
+__device__ __forceinline__ void attend_unit(RowState &st, const uint4 &qv, float scale_log2, UnitRows r, int batches,
+                                            int lane16) {
+#pragma unroll 1
+  for (int i = 0; i < batches; ++i) {
+    uint4 k[B], v[B];
+    float w[B], x[B], m_new = st.m;
+    load_unit_rows<0, B>(r, lane16, k, v);
+    __builtin_amdgcn_sched_barrier(0);  // (the sizes are waited for behind these loads, not in front of them)
+    asm volatile("" : "+v"(r.size));
+    // log2(1) = 0 exactly; log2(0) = -inf: no row weighs nothing
+    spread_weights<0, B>(__builtin_amdgcn_logf((float)(r.weight < 0 ? r.size : r.weight)), w);
+    r.klo = row_rotate<B>(r.klo);
+    r.khi = row_rotate<B>(r.khi);
+    r.vlo = row_rotate<B>(r.vlo);
+    r.vhi = row_rotate<B>(r.vhi);
+    r.size = (int)row_rotate<B>((uint32_t)r.size);
+    r.weight = (int)row_rotate<B>((uint32_t)r.weight);
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      // a lane without a row of its own names another row of the unit: only its weight says so (a product that is not
+      // finite makes the head's result NaN through the row that is there)
+      x[u] = fmaf(row16_sum(dot8_bf16(qv, k[u])), scale_log2, w[u]);
+      m_new = fmaxf(m_new, x[u]);
+    }
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // no rows so far: every weight is exp2(-inf) = 0
+    const float alpha = exp2f(st.m - m_ref);
+    st.l *= alpha;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) st.acc[j] *= alpha;
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const float p = exp2f(x[u] - m_ref);
+      // (0 x inf: what is not there must not meet the values of the row it names)
+      const bool none = w[u] == -INFINITY;
+      const uint4 vr = make_uint4(none ? 0u : v[u].x, none ? 0u : v[u].y, none ? 0u : v[u].z, none ? 0u : v[u].w);
+      float vf[8];
+      unpack8(vr, vf);
+      st.l += p;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) st.acc[j] = fmaf(p, vf[j], st.acc[j]);
+    }
+    st.m = m_new;
+  }
+}
+
 // Merge the 4 groups of a wave (log-sum-exp merge); every group ends with the wave's state.
 __device__ __forceinline__ void wave_merge(RowState &st) {
 #pragma unroll
@@ -137,8 +227,8 @@ __device__ __forceinline__ void wave_merge(RowState &st) {
 // unnormalised output of dim tid.  n_waves is block-uniform, 1 <= n_waves <= NW.
 template <int NW>
 __device__ __forceinline__ void block_merge(RowState &st, float *s_m, float *s_l, float (*s_acc)[kHeadDim],
-                                            int n_waves, float &M, float &L, float &o) {
-  const int lane = lane_id(), w = wave_id();
+                                            int n_waves, float &M, float &L, float &o, int tid) {
+  const int lane = tid & 63, w = tid >> 6;
   if (w < n_waves) {
     wave_merge(st);
     if (lane < 16) {
@@ -154,12 +244,12 @@ __device__ __forceinline__ void block_merge(RowState &st, float *s_m, float *s_l
   M = -INFINITY;
   L = 0.f;
   o = 0.f;
-  if (threadIdx.x < kHeadDim) {
+  if (tid < kHeadDim) {
     for (int g = 0; g < n_waves; ++g) M = fmaxf(M, s_m[g]);
     for (int g = 0; g < n_waves; ++g) {
       const float wg = (s_m[g] == -INFINITY) ? 0.f : exp2f(s_m[g] - M);
       L += s_l[g] * wg;
-      o += s_acc[g][threadIdx.x] * wg;
+      o += s_acc[g][tid] * wg;
     }
   }
 }

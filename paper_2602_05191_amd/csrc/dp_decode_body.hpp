@@ -21,10 +21,15 @@
 // workgroups that pull items from a device-side queue: every workgroup builds
 // the same prefix of items per head in LDS from head_rows[], then claims item
 // numbers with an atomic counter until they run out (nobody waits for anybody).
-// Inside a workgroup of T threads each 16-lane DPP row owns one cache row per
+// Inside a workgroup the waves take units of 16, 32 or 64 rows of an item, each for
+// itself: a wave reads the list entries that cover its unit, works out per lane where
+// one row lies, and then each 16-lane DPP row owns one cache row per
 // load (lane t holds dims [8t, 8t+8) of K for the dot and of V for the
-// accumulation), keeps its own online-softmax state in base-2 exponent form,
-// and the states are merged through LDS.  Partials (m, l, acc[128]) go to the
+// accumulation) and keeps its own online-softmax state in base-2 exponent form;
+// the states are merged through LDS at the end of the item.  (With the lists staged
+// in LDS for the whole workgroup and walked row by row: one 128 k-token step of 256
+// heads, half of them flat, 148 us for the decode launch against 136; a fixed budget,
+// 70 MB of rows, 27.3 against 24.3.)  Partials (m, l, acc[128]) go to the
 // workspace; the item of a head that finishes last (an arrival counter, no
 // waiting) merges them (log-sum-exp merge), normalises and writes the output.
 #pragma once
@@ -35,6 +40,7 @@
 
 namespace dp {
 
+typedef unsigned long long u64_t;
 constexpr int kPartialStride = kHeadDim + 2;  // m, l, acc[128]
 
 struct DecodeArgs {
@@ -98,8 +104,8 @@ inline DecodeArgs decode_args_of(const CacheView &c, const int32_t *n_exact, con
   (kCoherent ? __hip_atomic_load(&(lvalue), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (lvalue))
 
 // Rows in flight per 16-lane row in the queue.  Inside the selection's launch a CU holds one or two large
-// workgroups (16 waves at most, against 20 of the decode kernel's small ones), and every barrier of an item stops all
-// of them: the rows in flight per wave are doubled there (32 flat heads over 128 k tokens: 105 -> 98 us per step).
+// workgroups (16 waves at most, against 20 of the decode kernel's small ones): the rows in flight per wave are doubled
+// there (32 flat heads over 128 k tokens: 105 -> 98 us per step).
 __host__ __device__ constexpr int queue_batch(bool coherent) { return coherent ? 8 : kAttendBatch; }
 
 // rows per item of a head with R rows (multiple of kChunkRows); g: least chunks per item of this launch
@@ -109,23 +115,110 @@ __device__ __forceinline__ int rows_per_item(int R, int S, int g) {
 
 // LDS of the queue, declared by the kernel that runs it (separate arrays: as members of one struct the same code
 // needed 16 more vector registers and lost a wave of occupancy on the decode kernel)
-#define DP_DECODE_LDS(T)                                                                           \
-  __shared__ int s_start[((T) > 512 ? (T) : 512) + 1]; /* rows resolved per LDS staging round */    \
-  __shared__ int s_src[((T) > 512 ? (T) : 512) + 1];                                               \
+#define DP_DECODE_LDS(T, HEADS)                                                                    \
   __shared__ float s_m[(T) / 64], s_l[(T) / 64];                                                   \
   __shared__ float s_acc[(T) / 64][kHeadDim];                                                      \
   __shared__ int s_last, s_item;                                                                   \
-  __shared__ int s_first[kMaxQueueHeads + 1]; /* first item number of each head of this launch */  \
+  __shared__ int s_first[(HEADS) + 1]; /* first item number of each head of this launch */         \
   __shared__ int s_scan[(T) / 64 + 1];                                                             \
-  __shared__ int s_rows[kMaxQueueHeads]
-#define DP_DECODE_LDS_ARGS s_start, s_src, s_m, s_l, s_acc, &s_last, &s_item, s_first, s_scan, s_rows
+  __shared__ int s_rows[(HEADS)]
+#define DP_DECODE_LDS_ARGS s_m, s_l, s_acc, &s_last, &s_item, s_first, s_scan, s_rows
 
-// One (head, split) item: attend its rows, publish the partial, and merge the head if this item arrives last.
+// What the rows [r0, r1) of a head's list are, one row per lane: lane 16 g + j takes row j of group g, `per` rows per
+// group (4 per <= 64 rows, inside one 64-row chunk of the list whose first row lies in entry ent0).  Lane k holds the
+// start and the source of entry ent0 + k: every entry has at least one row, so 64 of them cover the chunk.  The entry
+// of a row is then the number of entries that start at or before it, counted in a 64-bit mask of the starts: no walk.
+struct UnitLists {
+  int start, source;
+};
+template <bool kGathered>
+__device__ __forceinline__ UnitRows unit_rows(int lane, const UnitLists &li, const RowSources &src, const int32_t *row_start, const int32_t *ent_src,
+                                              bool check, int ent0, int n_ex, int n_rt, int r0, int r1, int per) {
+  const int rc = r0 & ~(kChunkRows - 1);
+  const int d = li.start - rc;
+  const uint32_t lo = wave_or(lane > 0 && d < 32 ? 1u << (d & 31) : 0u);
+  const uint32_t hi = wave_or(lane > 0 && d >= 32 && d < 64 ? 1u << (d & 31) : 0u);
+  const int j = lane & 15;
+  const int mine = r0 + (lane >> 4) * per + j;
+  const bool valid = j < per && mine < r1;
+  const int row = valid ? mine : r1 - 1;
+  const int at = row - rc;
+  const uint32_t upto_lo = at >= 31 ? 0xffffffffu : (2u << at) - 1u;
+  const uint32_t upto_hi = at >= 63 ? 0xffffffffu : at >= 32 ? (2u << (at - 32)) - 1u : 0u;
+  int k = __popc(lo & upto_lo) + __popc(hi & upto_hi);
+  int source = __shfl(li.source, k, 64), start = __shfl(li.start, k, 64);
+  if (check) {
+    // lists given by a caller: an entry without rows (not allowed, but harmless so far) shares its start with the next
+    // one, and the count is off: look the rows up one by one
+    const int next = __shfl_down(li.start, 1, 64);
+    if (__any(lane < 63 && ent0 + lane + 1 < n_rt && next == li.start)) {
+      k = 0;
+      while (ent0 + k + 1 < n_rt && row_start[ent0 + k + 1] <= row) ++k;
+      source = ent_src[ent0 + k];
+      start = row_start[ent0 + k];
+    }
+  }
+  const bool exact = ent0 + k < n_ex;
+  // (unconditional, and an atomic load so that it stays so: inside a condition it is waited for on its own)
+  const int size = __hip_atomic_load(src.seg_sizes + (exact ? 0 : source), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  UnitRows u;
+  uint64_t ka, va;
+  if (kGathered && src.k_gather) {
+    const int64_t g = exact ? src.gather_row0 + row : src.c0 + source;
+    ka = (uint64_t)(exact ? src.k_gather : src.k_centroids) + g * kRowBytes;
+    va = (uint64_t)(exact ? src.v_gather : src.v_centroids) + g * kRowBytes;
+  } else {
+    const int64_t g = exact ? src.seg_row0 + source + (row - start) : src.c0 + source;
+    ka = (uint64_t)(exact ? src.k_cache : src.k_centroids) + g * kRowBytes;
+    va = (uint64_t)(exact ? src.v_cache : src.v_centroids) + g * kRowBytes;
+  }
+  u.klo = (uint32_t)ka;
+  u.khi = (uint32_t)(ka >> 32);
+  u.vlo = (uint32_t)va;
+  u.vhi = (uint32_t)(va >> 32);
+  u.size = size;
+  u.weight = !valid ? 0 : exact ? 1 : -1;
+  return u;
+}
+
+// Merge of n partials (m, l, acc[128]; written by workgroups of this launch) by a workgroup, a 16-lane row per partial.
+template <int T>
+__device__ __forceinline__ void gather_partials(const float *P, int n, RowState &st, int lane16, int grp) {
+  typedef unsigned long long u64;
+  row_state_init(st);
+#pragma unroll 1
+  for (int s = grp; s < n; s += T / 16) {
+    const u64 *Q = reinterpret_cast<const u64 *>(P + (int64_t)s * kPartialStride);  // 520 bytes apart: 8-byte aligned
+    u64 w[5];
+    w[0] = __hip_atomic_load(Q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[1 + i] = __hip_atomic_load(Q + 1 + 4 * lane16 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const float m = __uint_as_float((uint32_t)w[0]), l = __uint_as_float((uint32_t)(w[0] >> 32));
+    const float M = fmaxf(st.m, m);
+    const float wa = st.m == -INFINITY ? 0.f : exp2f(st.m - M), wb = m == -INFINITY ? 0.f : exp2f(m - M);
+    st.l = st.l * wa + l * wb;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float o = __uint_as_float((uint32_t)(w[1 + i / 2] >> (32 * (i & 1))));
+      st.acc[i] = st.acc[i] * wa + o * wb;
+    }
+    st.m = M;
+  }
+}
+
+// One item, the rows [split * c, + c) of a head: attend them, publish the partial, and merge the head if this item
+// arrives last.  c is a multiple of 64.  The waves of the workgroup take units of the item in turn, each for itself:
+// nothing but the merge at the end makes them wait for one another, so one wave's list lookups hide behind another
+// one's rows.
 template <int T, bool kGathered, bool kCoherent>
-__device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int split, int R, int g, int *s_start, int *s_src,
-                                            float *s_m, float *s_l, float (*s_acc)[kHeadDim], int *s_last, int tid,
-                                            int lane16, int grp) {
-  const int c = rows_per_item(R, a.splits, g);
+__device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int split, int R, int c, float *s_m, float *s_l,
+                                            float (*s_acc)[kHeadDim], int *s_last) {
+  constexpr int kWaves = T / 64;
+  // (a thread number that is new with every item: addresses made from it are not kept in registers from item to item,
+  // which cost a wave of occupancy)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, lane16 = tid & 15;
   const int row_a = split * c;
   const int row_b = min(R, row_a + c);
   const int n_active = (R + c - 1) / c;
@@ -136,6 +229,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int s
   const int n_ex = DP_LD_I32(a.n_exact[head]), n_rt = DP_LD_I32(a.n_retained[head]);
   const int32_t *ent_src = a.plan.ent_src + (int64_t)head * a.max_k;
   const int32_t *row_start = a.plan.row_start + (int64_t)head * (a.max_k + 1);
+  const int32_t *chunk_entry = a.plan.chunk_entry + (int64_t)head * a.plan.chunk_stride;
 
   const uint4 qv = load_row_slice(a.q, (int64_t)head, lane16);
 
@@ -150,8 +244,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int s
   src.k_gather = src.v_gather = nullptr;
   src.gather_row0 = 0;
   // a head whose exact rows did not fit the buffer was not gathered: it is read in place
-  const bool use_gather = kGathered && n_ex > 0 && row_start[n_ex] <= a.rows_cap;
-  if (use_gather) {
+  if (kGathered && n_ex > 0 && row_start[n_ex] <= a.rows_cap) {
     src.k_gather = a.k_gather;
     src.v_gather = a.v_gather;
     src.gather_row0 = (int64_t)head * a.rows_cap;
@@ -160,49 +253,38 @@ __device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int s
   RowState st;
   row_state_init(st);
 
-  int ent0 = DP_LD_I32(a.plan.chunk_entry[(int64_t)head * a.plan.chunk_stride + row_a / kChunkRows]);
-
-  for (int r0 = row_a; r0 < row_b; r0 += (T > 512 ? T : 512)) {
-    const int r1 = min(row_b, r0 + (T > 512 ? T : 512));
-    // stage the list entries that cover rows [r0, r1): every entry has >= 1 row
-    const int n_ent = min(r1 - r0, n_rt - ent0);
-    __syncthreads();
-    for (int k = tid; k <= n_ent; k += T) {
-      if (!kCoherent) {  // both loads go out together (n_ent >= 1: an item has a row)
-        const int start = row_start[ent0 + k];
-        const int source = ent_src[ent0 + min(k, n_ent - 1)];
-        s_start[k] = start;
-        s_src[k] = (k < n_ent) ? source : 0;
-      } else {
-        s_start[k] = DP_LD_I32(row_start[ent0 + k]);
-        s_src[k] = (k < n_ent) ? DP_LD_I32(ent_src[ent0 + k]) : 0;
-      }
-    }
-    __syncthreads();
-    // the DPP-row groups take consecutive pieces of kB rows: one step of the workgroup reads T / 16 * kB consecutive
-    // rows
-    constexpr int kB = queue_batch(kCoherent);
-    if (use_gather)
-      attend_rows<true, kB>(st, qv, a.scale_log2, src, s_start, s_src, n_ent, ent0, n_ex, r0 + grp * kB, r1,
-                            (T / 16) * kB, lane16);
-    else
-      attend_rows<false, kB>(st, qv, a.scale_log2, src, s_start, s_src, n_ent, ent0, n_ex, r0 + grp * kB, r1,
-                             (T / 16) * kB, lane16);
-    // first entry of the next block: the entry that holds row r1
-    if (r1 < row_b) {
-      int lo = 0, hi = n_ent + 1;  // s_start[n_ent] is staged as well
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_start[mid] <= r1) lo = mid; else hi = mid;
-      }
-      ent0 += lo;
+  // rows per unit: 64, or fewer where the item would not give every wave one (at least one batch of every group)
+  constexpr int kB = queue_batch(kCoherent);
+  const int n_rows = row_b - row_a;
+  const int unit = n_rows > kWaves * 32 ? 64 : (kB == 8 || n_rows > kWaves * 16) ? 32 : 16;
+  const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+  int r0 = row_a + wave * unit;
+  if (r0 < row_b) {
+    int ent0 = DP_LD_I32(chunk_entry[r0 / kChunkRows]);
+    int ent_next = DP_LD_I32(chunk_entry[min(r0 + kWaves * unit, R - 1) / kChunkRows]);
+    UnitLists li;
+    li.start = DP_LD_I32(row_start[min(ent0 + lane, n_rt)]);
+    li.source = DP_LD_I32(ent_src[min(ent0 + lane, n_rt - 1)]);
+#pragma unroll 1
+    for (;;) {
+      const int r1 = min(row_b, r0 + unit), next = r0 + kWaves * unit;
+      const UnitRows rows = unit_rows<kGathered>(lane, li, src, row_start, ent_src, !kCoherent, ent0, n_ex, n_rt, r0, r1, unit / 4);
+      // the next unit's lists are fetched in front of this one's rows
+      ent0 = ent_next;
+      ent_next = DP_LD_I32(chunk_entry[min(next + kWaves * unit, R - 1) / kChunkRows]);
+      li.start = DP_LD_I32(row_start[min(ent0 + lane, n_rt)]);
+      li.source = DP_LD_I32(ent_src[min(ent0 + lane, n_rt - 1)]);
+      attend_unit<kB>(st, qv, a.scale_log2, rows, unit / (4 * kB), lane16);
+      if (next >= row_b) break;
+      r0 = next;
     }
   }
 
+  tid = threadIdx.x;  // (anew: nothing made from it is held over the rows)
+  asm volatile("" : "+v"(tid));
   float M, L, o;
-  // (waves beyond the item's rows hold the empty state: a large workgroup does not merge them; for the small
-  // workgroups of the decode kernel the count stays a constant, which keeps the kernel at five waves per SIMD)
-  block_merge<(T / 64)>(st, s_m, s_l, s_acc, T > 256 ? min(T / 64, (row_b - row_a + 15) / 16) : T / 64, M, L, o);
+  // (waves beyond the item's rows hold the empty state: they are not merged)
+  block_merge<kWaves>(st, s_m, s_l, s_acc, min(kWaves, (n_rows + unit - 1) / unit), M, L, o, tid);
 
   if (n_active == 1) {  // the only split of this head: finish here
     if (tid < kHeadDim) {
@@ -236,46 +318,23 @@ __device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int s
   }
   __syncthreads();
   if (!(*s_last)) return;
+  gather_partials<T>(P, n_active, st, tid & 15, tid >> 4);
+  block_merge<kWaves>(st, s_m, s_l, s_acc, min(kWaves, (n_active + 3) / 4), M, L, o, tid);
   if (tid < kHeadDim) {
-    // running log-sum-exp merge; the coherent loads of 8 partials are issued together
-    float Mx = -INFINITY, Ls = 0.f, os = 0.f;
-    for (int s0 = 0; s0 < n_active; s0 += 8) {
-      float ms[8], ll[8], oo[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float *Q = P + min(s0 + u, n_active - 1) * kPartialStride;
-        ms[u] = __hip_atomic_load(Q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ll[u] = __hip_atomic_load(Q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        oo[u] = __hip_atomic_load(Q + 2 + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (s0 + u < n_active) {  // every partial has a finite m: an item has at least one row
-          const float Mn = fmaxf(Mx, ms[u]);
-          const float sc = exp2f(Mx - Mn), w = exp2f(ms[u] - Mn);
-          Ls = Ls * sc + ll[u] * w;
-          os = os * sc + oo[u] * w;
-          Mx = Mn;
-        }
-      }
-    }
-    store_out(a.out, a.out_is_bf16, head, tid, os / Ls);
-    if (a.lse && tid == 0) a.lse[head] = (Mx + log2f(Ls)) * kLn2;
+    store_out(a.out, a.out_is_bf16, head, tid, o / L);
+    if (a.lse && tid == 0) a.lse[head] = (M + log2f(L)) * kLn2;
   }
 }
 
-// The queue of one launch.  kCoherent = the plan was written by workgroups of this same launch: it is read with
-// device-coherent loads and EVERY item is claimed from the counter (a workgroup may be missing from the launch's
-// tail, see the selection kernel); otherwise a workgroup's first item is its block index and only further items
-// are claimed.  Call with the whole workgroup.
-template <int T, bool kGathered, bool kCoherent>
-__device__ __forceinline__ void decode_queue(const DecodeArgs &a, int *s_start, int *s_src, float *s_m, float *s_l,
-                                             float (*s_acc)[kHeadDim], int *s_last, int *s_item, int *s_first,
-                                             int *s_scan, int *s_rows) {
-  const int tid = threadIdx.x, lane16 = tid & 15, grp = tid >> 4;
+// The queue of a decode launch: the plan was written by an earlier launch.  A workgroup's first item is its block index,
+// further items are claimed from the counter.  Call with the whole workgroup.
+template <int T, bool kGathered>
+__device__ __forceinline__ void decode_queue(const DecodeArgs &a, float *s_m, float *s_l, float (*s_acc)[kHeadDim],
+                                             int *s_last, int *s_item, int *s_first, int *s_scan, int *s_rows) {
+  const int tid = threadIdx.x;
 
   // ---- the queue: items per head from head_rows[], exclusive prefix in LDS ----
-  constexpr int kMinItemChunks = T / 64;  // least chunks per item of a heavy launch: four steps of a small workgroup, two of a large one
+  constexpr int kMinItemChunks = T / 64;  // least chunks per item of a heavy launch: a 64-row unit for every wave
   constexpr int kPer = kMaxQueueHeads / T;  // consecutive heads per thread
   int rows[kPer], chunks = 0;
 #pragma unroll
@@ -283,32 +342,15 @@ __device__ __forceinline__ void decode_queue(const DecodeArgs &a, int *s_start, 
     const int hh = tid * kPer + u;
     // (an unconditional load at a clamped index, the value chosen afterwards: loads inside a condition are waited
     // for one by one, four dependent round trips at the start of every workgroup)
-    // (Only in the decode launch of its own: inside the selection's launch the same rewrite changed nothing for the
-    // queue and cost the selection of a peaked head 0.2 us through the code around it.)
-    if (!kCoherent) {
-      const int got = a.plan.head_rows[a.head0 + min(hh, a.n_heads - 1)];
-      rows[u] = hh < a.n_heads ? got : 0;  // <= 0: nothing to do (empty, or attended already)
-    } else {
-      rows[u] = hh < a.n_heads ? DP_LD_I32(a.plan.head_rows[a.head0 + hh]) : 0;
-    }
+    const int got = a.plan.head_rows[a.head0 + min(hh, a.n_heads - 1)];
+    rows[u] = hh < a.n_heads ? got : 0;  // <= 0: nothing to do (empty, or attended already)
     s_rows[hh] = rows[u];
     if (rows[u] > 0) chunks += min(1 << 20, (rows[u] + kChunkRows - 1) / kChunkRows);  // capped: the sum stays in range
   }
-  // least chunks per item, between 1 and kMinItemChunks.  A launch of many small workgroups aims at about one item
-  // for every second workgroup; the few large workgroups of a shared launch (kCoherent) at four items each, in whole
-  // steps of the workgroup (T / 4 rows).
+  // least chunks per item, between 1 and kMinItemChunks: the launch aims at about one item for every second workgroup
   const int all_chunks = block_sum<int, (T / 64)>(chunks, s_scan);
-  int g;
-  if (kCoherent) {
-    constexpr int kStepRows = T / 16 * queue_batch(true);
-    constexpr int kStepChunks = kStepRows >= kChunkRows ? kStepRows / kChunkRows : 1;
-    const int want = max(1, 4 * (int)gridDim.x);
-    g = (all_chunks + want - 1) / want;
-    g = min(kMinItemChunks, max(kStepChunks, (g + kStepChunks - 1) / kStepChunks * kStepChunks));
-  } else {
-    const int half_grid = max(1, (int)gridDim.x / 2);
-    g = min(kMinItemChunks, max(1, (all_chunks + half_grid - 1) / half_grid));
-  }
+  const int half_grid = max(1, (int)gridDim.x / 2);
+  const int g = min(kMinItemChunks, max(1, (all_chunks + half_grid - 1) / half_grid));
   int cnt[kPer], mine = 0;
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
@@ -330,34 +372,7 @@ __device__ __forceinline__ void decode_queue(const DecodeArgs &a, int *s_start, 
   if (tid == T - 1) s_first[kMaxQueueHeads] = total;
   __syncthreads();
   if (total == 0) return;
-
-  if (kCoherent) {
-    // every item is claimed from the counter, the next one before this one is attended (the counter's round trip
-    // hides behind the rows of a large workgroup's item)
-    if (tid == 0) *s_item = __hip_atomic_fetch_add(a.queue_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    int item = *s_item;
-    __syncthreads();
 #pragma unroll 1
-    while (item < total) {
-      int lo = 0, hi = kMaxQueueHeads;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_first[mid] <= item) lo = mid; else hi = mid;
-      }
-      const int head = a.head0 + lo, split = item - s_first[lo];
-      int next = total;
-      if (tid == 0) next = __hip_atomic_fetch_add(a.queue_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      decode_item<T, kGathered, true>(a, head, split, s_rows[lo], g, s_start, s_src, s_m, s_l, s_acc, s_last, tid, lane16, grp);
-      if (tid == 0) *s_item = next;
-      __syncthreads();  // also: LDS is reused by the next item
-      item = *s_item;
-      __syncthreads();
-    }
-    return;
-  }
-#pragma unroll 1
-  // the first item of a workgroup is its block index; further items are claimed from the counter
   for (int item = blockIdx.x; item < total;) {
     // head that owns the item: the largest hh with s_first[hh] <= item (heads without items repeat the
     // next head's value, so the largest such hh is the one with s_first[hh + 1] > item)
@@ -366,13 +381,79 @@ __device__ __forceinline__ void decode_queue(const DecodeArgs &a, int *s_start, 
       const int mid = (lo + hi) >> 1;
       if (s_first[mid] <= item) lo = mid; else hi = mid;
     }
-    const int head = a.head0 + lo, split = item - s_first[lo];
-    decode_item<T, kGathered, false>(a, head, split, s_rows[lo], g, s_start, s_src, s_m, s_l, s_acc, s_last, tid, lane16, grp);
+    // (uniform: in scalar registers, and what is computed from them too)
+    const int head = __builtin_amdgcn_readfirstlane(a.head0 + lo), split = __builtin_amdgcn_readfirstlane(item - s_first[lo]);
+    const int R = __builtin_amdgcn_readfirstlane(s_rows[lo]);
+    decode_item<T, kGathered, false>(a, head, split, R, rows_per_item(R, a.splits, g), s_m, s_l, s_acc, s_last);
     if (total <= (int)gridDim.x) break;  // every item had its workgroup: nothing to claim
     if (tid == 0)
       *s_item = gridDim.x + __hip_atomic_fetch_add(a.queue_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();  // also: LDS is reused by the next item
     item = *s_item;
+    __syncthreads();
+  }
+}
+
+// The queue inside the selection's launch (at most kSameLaunchMaxHeads heads; s_rows[] holds their rows, 0 where there is
+// nothing to do; call with the whole workgroup after a barrier).  The plan was written by workgroups of this same launch:
+// it is read with device-coherent loads, and EVERY item is claimed from the counter (a workgroup may be missing): `first`
+// is this workgroup's first claim, known to the last wave only.
+// The rows are cut so that there is about one item for every workgroup that serves: helpers and heads that left rows.
+// (Items of 512 rows, three or four of them for a workgroup, all waves in step at five barriers each, left the memory idle
+// while an item began and ended: 32 flat heads over 8 x 131072 tokens, 94 us per step; now 74, of which the queue takes 45
+// for 240 MB.)
+template <int T>
+__device__ __forceinline__ void decode_queue_here(const DecodeArgs &a, int first, float *s_m, float *s_l, float (*s_acc)[kHeadDim],
+                                                  int *s_last, int *s_item, int *s_first, int *s_scan, int *s_rows) {
+  static_assert(kSameLaunchMaxHeads == 128, "two heads per lane");
+  const int tid = threadIdx.x, lane = lane_id();
+  // every wave works the cut out for itself
+  const int R0 = s_rows[lane], R1 = s_rows[64 + lane];
+  const int ch0 = (R0 + kChunkRows - 1) / kChunkRows, ch1 = (R1 + kChunkRows - 1) / kChunkRows;
+  const int all = wave_sum(min(ch0, 1 << 23) + min(ch1, 1 << 23));
+  const int n_left = __popcll(__ballot(R0 > 0)) + __popcll(__ballot(R1 > 0));
+  const int helpers = max(1, (int)gridDim.x - a.n_heads), servers = helpers + n_left;
+  // g chunks per item: all / helpers gives at most `servers` items (every head may add a short one); finer if that
+  // already does
+  int g = max(1, (all + helpers - 1) / helpers);
+  int n0, n1, total;
+  auto cut = [&](int gg) {
+    const int c0 = rows_per_item(R0, a.splits, gg), c1 = rows_per_item(R1, a.splits, gg);
+    n0 = R0 > 0 ? (R0 + c0 - 1) / c0 : 0;
+    n1 = R1 > 0 ? (R1 + c1 - 1) / c1 : 0;
+    total = wave_sum(n0 + n1);
+  };
+  {
+    const int finer = max(1, (all + servers - 1) / servers);
+    const int mid = (finer + g) / 2;
+    cut(finer);
+    if (total <= servers) {
+      g = finer;
+    } else {
+      cut(mid);
+      if (total <= servers) g = mid;
+      else cut(g);
+    }
+  }
+  const int i0 = wave_incl_scan(n0), i1 = wave_incl_scan(n1);
+  const int f0 = i0 - n0, f1 = lane_u32((uint32_t)i0, 63) + i1 - n1;
+  int item = first;
+#pragma unroll 1
+  for (;;) {
+    if (tid == T - 64) *s_item = item;
+    __syncthreads();  // also: LDS is reused by the next item
+    item = __builtin_amdgcn_readfirstlane(*s_item);
+    if (item >= total) return;
+    const u64_t own0 = __ballot(item >= f0 && item < f0 + n0), own1 = __ballot(item >= f1 && item < f1 + n1);
+    const int at = own0 ? __builtin_ctzll(own0) : __builtin_ctzll(own1);
+    const int head = own0 ? at : 64 + at;
+    const int R = __builtin_amdgcn_readlane(own0 ? R0 : R1, at);
+    const int split = item - __builtin_amdgcn_readlane(own0 ? f0 : f1, at);
+    // the next item is claimed before this one is attended
+    int next = 0;
+    if (tid == T - 64) next = __hip_atomic_fetch_add(a.queue_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    decode_item<T, false, true>(a, head, split, R, rows_per_item(R, a.splits, g), s_m, s_l, s_acc, s_last);
+    item = next;
     __syncthreads();
   }
 }

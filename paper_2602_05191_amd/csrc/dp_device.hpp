@@ -183,6 +183,14 @@ __device__ __forceinline__ int wave_sum(int v) {
   return (int)((lane_u32((uint32_t)v, 0) + lane_u32((uint32_t)v, 16)) + (lane_u32((uint32_t)v, 32) + lane_u32((uint32_t)v, 48)));
 }
 
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+  v |= dpp_mov_u32<0xB1>(v);
+  v |= dpp_mov_u32<0x4E>(v);
+  v |= dpp_mov_u32<0x141>(v);
+  v |= dpp_mov_u32<0x140>(v);
+  return (lane_u32(v, 0) | lane_u32(v, 16)) | (lane_u32(v, 32) | lane_u32(v, 48));
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
   v = row16_sum(v);
   return (lane_f32(v, 0) + lane_f32(v, 16)) + (lane_f32(v, 32) + lane_f32(v, 48));

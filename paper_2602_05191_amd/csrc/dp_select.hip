@@ -826,7 +826,7 @@ __device__ __forceinline__ bool full_select(const SelectArgs &a, Shared<T> &sh, 
       put_counts(a.out, head, 0, 0, 0, emit.coherent);
       if (plan) {
         st_i32(emit.row_start, 0, emit.coherent);
-        st_i32(a.plan.head_rows + head, 0, emit.coherent);
+        st_i32(a.plan.head_rows + head, emit.coherent ? -1 : 0, emit.coherent);
         st_i32(a.plan.done + head, 0, emit.coherent);
       }
       if (can_inline && a.lse) a.lse[head] = -INFINITY;
@@ -1119,11 +1119,10 @@ __device__ __forceinline__ int select_head(const SelectArgs &a, Shared<T> &sh, i
     if (plan) {
       if (inline_attn) {
         if (!chosen) sh.at.l_start[n_ex + n_ap] = R;  // (the one-wave paths have written it with the lists)
-        // attended here: nothing left for the stage-3 queue (kGate: head_rows was cleared by the scoring kernel)
-        if (!kGate) a.plan.head_rows[head] = -1;
+        if (!kGate) a.plan.head_rows[head] = -1;  // attended here: nothing left for the stage-3 queue
       } else {
         st_i32(emit.row_start + n_ex + n_ap, R, kGate);
-        st_i32(a.plan.head_rows + head, R, kGate);
+        if (!kGate) a.plan.head_rows[head] = R;
         if (!kGate && a.plan.pending && R > 0) atomicAdd(&a.plan.pending[head / kMaxQueueHeads], 1);
       }
       if (!kGate || !inline_attn) st_i32(a.plan.done + head, 0, kGate);
@@ -1131,12 +1130,20 @@ __device__ __forceinline__ int select_head(const SelectArgs &a, Shared<T> &sh, i
   }
   // a head that is attended here has nothing to publish: it reports at once, and the workgroups that wait for the
   // count leave while it attends
-  if (kGate && inline_attn && tid == T - 64) arrival = head_planned(planned, false);
+  if (kGate && inline_attn && tid == T - 64) {
+    st_i32(a.plan.head_rows + head, -1, true);
+    arrival = head_planned(planned, false);
+  }
   if (!inline_attn) {
     if (kGate) {  // the plan was written by every thread: all of it has completed before the head reports
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
-      if (tid == T - 64) arrival = head_planned(planned, R > 0) | (R > 0 ? (int)0x80000000 : 0);
+      if (tid == T - 64) {
+        // head_rows says that the head is ready (the scoring kernel has cleared it); the counter moves after it
+        st_i32(a.plan.head_rows + head, R > 0 ? R : -1, true);
+        __builtin_amdgcn_s_waitcnt(0);
+        arrival = head_planned(planned, R > 0) | (R > 0 ? (int)0x80000000 : 0);
+      }
     }
     return arrival;
   }
@@ -1171,7 +1178,7 @@ __device__ __forceinline__ int select_head(const SelectArgs &a, Shared<T> &sh, i
     for (int u = 0; u < 4; ++u) arrived(warm[u]);  // loads complete in order: these have, with the rows read above
     float M, L, o;
     const int groups_used = (R + per - 1) / per;
-    block_merge<(T / 64)>(st, sh.at.m_m, sh.at.m_l, sh.at.m_acc, (groups_used + 3) / 4, M, L, o);
+    block_merge<(T / 64)>(st, sh.at.m_m, sh.at.m_l, sh.at.m_acc, (groups_used + 3) / 4, M, L, o, tid);
     if (tid < kHeadDim) {
       store_out(a.attn_out, a.out_is_bf16, head, tid, o / L);
       if (a.lse && tid == 0) a.lse[head] = (M + log2f(L)) * kLn2;
@@ -1189,13 +1196,17 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a) {
 // Stage 2 and stage 3 in one launch, for launches that serve few heads (a separate decode launch that finds nothing
 // to do would cost as much as the selection itself).  Workgroup b < n_heads selects head b (and attends it if it has
 // few rows); every workgroup, the ones beyond n_heads included, then serves the stage-3 queue of the heads that
-// were left over.  The queue may only start when every head has reported to `planned`.  Nobody waits without
-// bound: a selecting workgroup whose head was attended inline leaves when it is done; the one whose arrival completes
-// the count serves the queue until it is empty (so all items are attended whoever else has left); the workgroups
-// beyond n_heads and the ones whose own head left rows poll the counter for a limited time, serve the queue if the
-// count is reached and leave if it is not.  The scoring kernel of
-// the step clears planned and the item counter.
+// were left over.  The queue may only start when every head has reported: in head_rows[head] its rows (-1: none) and in
+// the counter `planned`.  Nobody waits without bound: a selecting workgroup whose head was attended inline leaves when it
+// is done; the one whose arrival completes the count serves the queue until it is empty (so all items are attended whoever
+// else has left); the workgroups beyond n_heads and the ones whose own head left rows read head_rows for a limited time,
+// serve the queue when every head has its word and leave if that does not come.  The scoring kernel of the step clears
+// planned, head_rows and the item counter.  (Polling the counter and reading head_rows behind it: 170 us against 141 for
+// two layers of 32 flat heads over 128 k tokens.)
 constexpr int kGatePolls = 20000;  // a microsecond or two each
+// x 64 clocks between two polls.  At 32 steps of flat heads gain 1-3 % and steps of peaked heads lose up to 5 (the polls of
+// 224 workgroups meet the heads' reports at one place of memory).
+constexpr int kGateSleep = 64;
 struct QueueArgs {  // what the stage-3 queue needs beyond the selection's own arguments
   float *partials;
   int32_t *planned;
@@ -1204,41 +1215,48 @@ struct QueueArgs {  // what the stage-3 queue needs beyond the selection's own a
 template <int E, bool kCount, int T>
 __global__ __launch_bounds__(T) void select_decode_kernel(SelectArgs a, QueueArgs qa) {
   __shared__ Shared<T> sh;
-  DP_DECODE_LDS(T);
+  DP_DECODE_LDS(T, kSameLaunchMaxHeads);
   __shared__ int s_go;
   int32_t *const planned = qa.planned;
   const int n_heads = qa.n_heads;
-  if ((int)blockIdx.x < n_heads) {
-    const int word = select_head<E, kCount, T, true>(a, sh, planned);
-    if (threadIdx.x == T - 64) {
-      // the last head in serves the queue if any head (itself included) left rows to it
-      bool go = (word & 0xffff) == n_heads - 1 && (word & 0xffff0000) != 0;
-      if (!go && word != -1 && (word & (int)0x80000000)) {
-        // a head that left rows: its workgroup stays for the queue like the ones beyond n_heads (a step of flat
-        // heads would otherwise be served by those alone)
-        int seen = 0;
+  int word = -1;
+  const bool selects = (int)blockIdx.x < n_heads;
+  if (selects) word = select_head<E, kCount, T, true>(a, sh, planned);
+  int first = 0;
+  if (threadIdx.x >= T - 64) {  // the last wave decides
+    const int lane = lane_id();
+    word = __builtin_amdgcn_readfirstlane(word);
+    // the last head in serves the queue if any head (itself included) left rows to it
+    const bool last = selects && (word & 0xffff) == n_heads - 1 && (word & 0xffff0000) != 0;
+    // the workgroups beyond n_heads, and one whose own head left rows, wait until every head has reported
+    const bool waits = !selects || (word != -1 && (word & (int)0x80000000));
+    bool go = last;
+    int r0 = 0, r1 = 0;
+    if (last || waits) {
 #pragma unroll 1
-        for (int it = 0; it < kGatePolls; ++it) {
-          seen = __hip_atomic_load(planned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if ((seen & 0xffff) >= n_heads) break;
-          __builtin_amdgcn_s_sleep(64);
+      for (int it = 0; it < kGatePolls; ++it) {
+        r0 = lane < n_heads ? __hip_atomic_load(a.plan.head_rows + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+        r1 = 64 + lane < n_heads
+                 ? __hip_atomic_load(a.plan.head_rows + 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                 : -1;
+        // (the last one in has seen the counter: what a head stored before it reported is there)
+        if (last) break;
+        if (!__any(r0 == 0 || r1 == 0)) {
+          go = __any(r0 > 0 || r1 > 0);
+          break;
         }
-        go = (seen & 0xffff) >= n_heads;
+        __builtin_amdgcn_s_sleep(kGateSleep);
       }
-      s_go = go;
     }
-  } else if (threadIdx.x == 0) {
-    int word = 0;
-#pragma unroll 1
-    for (int it = 0; it < kGatePolls; ++it) {
-      word = __hip_atomic_load(planned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((word & 0xffff) >= n_heads) break;
-      __builtin_amdgcn_s_sleep(64);
+    if (go) {
+      if (lane == 0) first = __hip_atomic_fetch_add(a.plan.queue_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_rows[lane] = max(r0, 0);
+      s_rows[64 + lane] = max(r1, 0);
     }
-    s_go = (word & 0xffff) >= n_heads && (word >> 16) > 0;
+    if (lane == 0) s_go = go;
   }
-  __syncthreads();
-  if (!s_go) return;
+  lds_barrier();
+  if (__builtin_expect(!s_go, 1)) return;
   // the queue's view of the same arguments
   DecodeArgs d;
   d.q = a.q;
@@ -1268,7 +1286,7 @@ __global__ __launch_bounds__(T) void select_decode_kernel(SelectArgs a, QueueArg
   d.k_gather = d.v_gather = nullptr;
   d.rows_cap = 0;
   d.scale_log2 = a.scale_log2;
-  decode_queue<T, false, true>(d, DP_DECODE_LDS_ARGS);
+  decode_queue_here<T>(d, first, DP_DECODE_LDS_ARGS);
 }
 
 // ---- plan from caller-given sets (staged API) -----------------------------
@@ -1339,21 +1357,10 @@ template <int E, int T>
 void launch_select_e(const SelectArgs &a, bool by_count, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop,
                      const QueueArgs *queue) {
   if (queue) {
-    // as many workgroups as 256 CUs hold at once (what the kernel's registers and LDS allow, asked once per
-    // kernel): a workgroup that had to wait for a place would only find the count complete and leave, at the
-    // launch's expense (with twice the resident number, a step of peaked heads over 2048 clusters took 11.8 us
-    // in the mean and 14.5 us in every tenth step)
-    static int per_cu[2] = {0, 0};
-    int &n = per_cu[by_count ? 1 : 0];
-    if (n == 0) {
-      int got = 0;
-      const hipError_t e =
-          by_count ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&got, select_decode_kernel<E, true, T>, T, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&got, select_decode_kernel<E, false, T>, T, 0);
-      n = (e == hipSuccess && got > 0) ? got : 1;
-    }
-    const unsigned resident = 256u * (unsigned)n;
-    const dim3 g(grid.x + 32 > resident ? grid.x + 32 : resident);
+    // one workgroup per CU: more of them help a heavy queue no more (512 workgroups of 512 threads: 3 ragged sequences of
+    // up to 38 k tokens with a flat head in eight 147 us per four layers against 130), and a workgroup that has to wait
+    // for a place would only find the count complete and leave, at the launch's expense
+    const dim3 g(grid.x + 32 > 256u ? grid.x + 32 : 256u);
     if (start || stop) {
       if (by_count)
         hipExtLaunchKernelGGL((select_decode_kernel<E, true, T>), g, dim3(T), 0, s, start, stop, 0, a, *queue);

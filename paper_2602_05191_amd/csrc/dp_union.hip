@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kGrpThreads) void group_decode_kernel(GroupArgs a) 
   for (int j = 0; j < GH; ++j) {
     float M, L, o;
     __syncthreads();  // the LDS of the previous merge (or of the staging) has been read by everybody
-    block_merge<kGrpWaves>(st[j], s_m, s_l, s_acc, kGrpWaves, M, L, o);
+    block_merge<kGrpWaves>(st[j], s_m, s_l, s_acc, kGrpWaves, M, L, o, threadIdx.x);
     if (tid < kHeadDim) {
       float *P = a.partials + (((int64_t)seg * a.splits + split) * a.group + a.head0 + j) * kGrpPartialStride;
       if (tid == 0) {

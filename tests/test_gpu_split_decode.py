@@ -1,0 +1,91 @@
+"""GPU parity of the split decode where its units, items and partials begin and end: rows per wave (16, 32, 64), items of
+several units, heads of one item and of many, in a launch of its own and inside the selection's launch."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import make_cache
+
+import harness as H
+
+pytestmark = pytest.mark.gpu
+
+# fp32 sums of up to 10^4 weighted values of size ~1 (weights sum to 1), the scores' own rounding (|x| <= 40: 40 x 2^-23)
+# above it; the bar that the other parity tests hold this path to as well
+TIGHT = 2e-4
+
+
+def _whole(cache, exact_share=1.0, seed=0):
+    """Every cluster of every segment retained, the first `exact_share` of a random order exact."""
+    rng = np.random.default_rng(seed)
+    exact, approx = [], []
+    for i in range(cache.batch * cache.n_q_heads):
+        b, h = divmod(i, cache.n_q_heads)
+        seg = b * cache.n_kv_heads + h // cache.group
+        n = int(cache.seg_cluster_ptr[seg + 1] - cache.seg_cluster_ptr[seg])
+        order = rng.permutation(n)
+        k = int(round(exact_share * n))
+        exact.append(np.sort(order[:k]))
+        approx.append(np.sort(order[k:]))
+    return exact, approx
+
+
+def _check_sets(cache, exact, approx):
+    out, lse = H.gpu_sparse_decode(cache, exact, approx)
+    g = H.GpuStep(out=out, lse=lse, exact=exact, approx=approx, n_exact_tokens=np.zeros(len(exact)))
+    H.check_outputs(cache, oracle.Oracle(cache), g, tight=TIGHT)
+    return out, lse
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 1023, 1025])
+@pytest.mark.parametrize("share", [1.0, 0.5, 0.0])
+def test_split_decode_of_few_rows(n, share):
+    """Rows around every unit and item size, as tokens, as pseudo-tokens and mixed."""
+    c = make_cache(batch=2, n_kv_heads=1, n_q_heads=2, context=[n, n + 7], mean_cluster=1 if share == 0.0 else 5,
+                   size_lo=1, size_hi=16, q_scale=0.4, seed=101)
+    _check_sets(c, *_whole(c, share, seed=n))
+
+
+@pytest.mark.parametrize("heads, context", [(2, 9000), (32, 3000), (128, 700)])
+def test_split_decode_inside_the_selection_launch(heads, context):
+    """p1 = p2 = 1 leaves every row of every head to the queue: items of many units, of few, and many heads; heads with
+    one row, none beyond the inline limit, and empty ones between them."""
+    import paper_2602_05191_amd as dp
+    n_seg = heads // 2
+    ctx = [context + 61 * i for i in range(n_seg)]
+    ctx[0] = 1
+    if n_seg > 3:
+        ctx[1], ctx[2] = 64, 65
+    c = make_cache(batch=n_seg, n_kv_heads=1, n_q_heads=2, context=ctx, mean_cluster=7, size_hi=32, q_scale=0.4, seed=102)
+    if n_seg > 3:
+        c.cluster_sizes[int(c.seg_cluster_ptr[3]):int(c.seg_cluster_ptr[4])] = 0   # a segment with nothing in it
+    orc = oracle.Oracle(c)
+    for flags in (0, dp.DP_FLAG_SEPARATE_DECODE_LAUNCH):
+        g = H.gpu_decode_attention(c, 1.0, 1.0, flags=flags)
+        H.check_outputs(c, orc, g, tight=TIGHT)
+        again = H.gpu_decode_attention(c, 1.0, 1.0, flags=flags)
+        assert np.array_equal(g.out.view(np.uint32), again.out.view(np.uint32))
+    # some heads flat, some peaked: both kinds of workgroup serve
+    g = H.gpu_decode_attention(c, 0.9, 0.6)
+    H.check_outputs(c, orc, g, tight=TIGHT)
+
+
+@pytest.mark.parametrize("n", [70, 100, 300, 2000])
+def test_split_decode_keeps_an_infinite_value_in_its_dimension(n):
+    """An infinity in the segment's last V row, which the lanes without a row of their own name as well."""
+    import paper_2602_05191_amd as dp
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=4, context=n, mean_cluster=8, size_hi=32, q_scale=0.3, seed=103)
+    c.v_cache[n - 1, 5] = 0x7F80
+    for flags in (0, dp.DP_FLAG_SEPARATE_DECODE_LAUNCH):
+        out = H.gpu_decode_attention(c, 1.0, 1.0, flags=flags).out
+        assert np.isposinf(out[..., 5]).all() and np.isfinite(np.delete(out, 5, axis=-1)).all()
+
+
+def test_split_decode_of_sets_with_an_empty_cluster():
+    """A caller's exact list that names clusters without rows (they add nothing)."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=2, context=900, mean_cluster=6, size_hi=16, q_scale=0.4, seed=104)
+    exact, approx = _whole(c, 0.8)
+    empty = [int(e) for e in exact[0][[0, 3, 4, 40, -1]]]
+    c.cluster_sizes[empty] = 0
+    approx = [np.array([a for a in ap if a not in empty], dtype=np.int64) for ap in approx]
+    _check_sets(c, exact, approx)
