@@ -77,7 +77,8 @@ __device__ __forceinline__ void publish_summary(const float (&v)[4], bool writer
 // bf16 dot instruction and the 16 partial dots are summed with DPP adds.  2.25 vector instructions per cluster and
 // head: up to G = 4 they hide behind the loads and the wholly contiguous load pattern streams faster.
 constexpr int kValuRows = 4;  // centroid rows in flight per 16-lane row; 16 rows x 4 = the 64 clusters of a workgroup
-template <int GH>
+// kStream: the centroids are read with non-temporal loads (the rule is at the launch).
+template <int GH, bool kStream>
 __global__ __launch_bounds__(kScoreThreads) void score_valu_kernel(
     const void *k_centroids, const int32_t *cluster_sizes, const void *q,
     const int32_t *__restrict__ seg_ptr, int uniform_kc, int n_kv_heads, int n_q_heads, int group, int head0, ScoreArgs a) {
@@ -106,8 +107,13 @@ __global__ __launch_bounds__(kScoreThreads) void score_valu_kernel(
   uint4 raw[kValuRows];
   int size[kValuRows];
 #pragma unroll
-  for (int k = 0; k < kValuRows; ++k)
-    raw[k] = (i0 + k < kc) ? load_row_slice(k_centroids, (int64_t)(c0 + i0 + k), lane16) : make_uint4(0, 0, 0, 0);
+  for (int k = 0; k < kValuRows; ++k) {
+    raw[k] = make_uint4(0, 0, 0, 0);
+    if (i0 + k < kc) {
+      const char *row = static_cast<const char *>(k_centroids) + (int64_t)(c0 + i0 + k) * kRowBytes + lane16 * 16;
+      raw[k] = kStream ? load_stream16(row) : *reinterpret_cast<const uint4 *>(row);
+    }
+  }
   // sizes: one dword per row, the same address for the 16 lanes of the group (a broadcast load; wider
   // or masked loads of the four sizes measured slower)
 #pragma unroll
@@ -265,12 +271,19 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(
 
 #define HOT_ARGS(a) (a).k_centroids, (a).cluster_sizes, (a).q, (a).seg_cluster_ptr, (a).uniform_kc, (a).n_kv_heads, (a).n_q_heads, (a).group, (a).head0
 
-template <int GH>
+template <int GH, bool kStream>
 void launch_valu(const ScoreArgs &a, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   if (start || stop)
-    hipExtLaunchKernelGGL(score_valu_kernel<GH>, grid, dim3(kScoreThreads), 0, s, start, stop, 0, HOT_ARGS(a), a);
+    hipExtLaunchKernelGGL((score_valu_kernel<GH, kStream>), grid, dim3(kScoreThreads), 0, s, start, stop, 0, HOT_ARGS(a), a);
   else
-    hipLaunchKernelGGL(score_valu_kernel<GH>, grid, dim3(kScoreThreads), 0, s, HOT_ARGS(a), a);
+    hipLaunchKernelGGL((score_valu_kernel<GH, kStream>), grid, dim3(kScoreThreads), 0, s, HOT_ARGS(a), a);
+}
+template <int GH>
+void launch_valu(const ScoreArgs &a, bool stream, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  if (stream)
+    launch_valu<GH, true>(a, grid, s, start, stop);
+  else
+    launch_valu<GH, false>(a, grid, s, start, stop);
 }
 
 template <int RT>
@@ -302,6 +315,15 @@ hipError_t launch_score(const CacheView &c, float *logits, hipStream_t s, hipEve
   if (c.group <= kScoreValuMaxGroup) {
     // one pass: 4, 2 or 1 heads at a time
     const dim3 vgrid((c.max_clusters_per_seg + kScoreTile - 1) / kScoreTile, c.batch * c.n_kv_heads);
+    // Whether the centroids are read with non-temporal loads.  They are for launches that read 1.5 to 24 MiB of them, where
+    // a step's layers come from memory anyway and a plain stream is in the way of the next kernel's reads: 8 x 2048
+    // clusters 11.3 -> 10.6 us per step (32 layers), 8 x 8192 14.3 -> 13.5 (12 layers; one layer again and again 13.2 ->
+    // 12.6).  Below, a launch is all latency (256 clusters: 9.0 against 9.2).  Above, a single layer that is scored again
+    // and again (128 segments of 500 to 2000 clusters, 33 MB: about what the L2s hold) loses 0.4 us of 21.4, while six
+    // such layers in turn would gain (23.9 -> 22.3); that the host cannot tell.  (On steps of flat heads, which read
+    // centroids again as pseudo-tokens, it costs 1 %.)
+    const int64_t bytes = (int64_t)c.max_clusters_per_seg * c.batch * c.n_kv_heads * kRowBytes;
+    const bool stream = bytes >= (3 << 19) && bytes <= (24 << 20);
     int h0 = 0;
     while (h0 < c.group) {
       const int left = c.group - h0, gh = left >= 4 ? 4 : left >= 2 ? 2 : 1;
@@ -309,9 +331,9 @@ hipError_t launch_score(const CacheView &c, float *logits, hipStream_t s, hipEve
       if (h0 > 0) a.zero_words = nullptr;  // cleared once, by the first pass
       hipEvent_t ev0 = (h0 == 0) ? start : nullptr, ev1 = (h0 + gh >= c.group) ? stop : nullptr;
       switch (gh) {
-        case 4: launch_valu<4>(a, vgrid, s, ev0, ev1); break;
-        case 2: launch_valu<2>(a, vgrid, s, ev0, ev1); break;
-        default: launch_valu<1>(a, vgrid, s, ev0, ev1); break;
+        case 4: launch_valu<4>(a, stream, vgrid, s, ev0, ev1); break;
+        case 2: launch_valu<2>(a, stream, vgrid, s, ev0, ev1); break;
+        default: launch_valu<1>(a, stream, vgrid, s, ev0, ev1); break;
       }
       h0 += gh;
     }
