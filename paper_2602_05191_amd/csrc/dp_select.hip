@@ -753,19 +753,28 @@ __device__ __forceinline__ void load_head_inputs(const SelectArgs &a, int c0, in
   }
 }
 
+// Rows of a head that its own workgroup attends although the search has taken its time already.  With the queue in this
+// launch (`gate`) a list costs some 10 us there until it is merged (every head has to report first), as much as the
+// workgroup needs for all the rows its lists hold: 128 flat heads over 4.5 k tokens 27.7 -> 25.3 us per step, 4 heads over
+// 4.5 k, two of them flat, 19.2 -> 16.9.  With a decode launch behind this one, a head per CU: 256 (a budget of 2 heads
+// over 4.5 k tokens 17.6 -> 15.9: nothing is left for that launch).  More heads than that come in rounds, and what holds
+// up a round costs more than it saves (256 heads over 11 k tokens, half of them flat: 39.8 at 64 and 128 rows, 41.2 at 256).
+template <int T>
+__device__ __forceinline__ int general_inline_rows(bool gate) {
+  return gate ? inline_rows_of(T) : gridDim.x <= 128 ? 256 : 64;
+}
+
 // The selection proper for one head (one workgroup) on the thread's loaded inputs: fast path for a peaked head,
 // general threshold search otherwise; emits the lists (and the plan) and returns the three counts.  Returns false
 // when the head had no candidate at all and has been finished here (counts, zero output).  known_max: the head's max
 // logit if the caller has it already (NaN if not).  inline_limit: the most rows of this head that are worth
-// attending in this workgroup (a head that took the general path has used up its time: 64 rows, which four waves
-// attend in one round of loads; a longer list goes to the split decode).
+// attending in this workgroup (general_inline_rows below for a head that took the general path).
 template <int E, bool kCount, int T>
 __device__ __forceinline__ bool full_select(const SelectArgs &a, Shared<T> &sh, Emit &emit, int head, int c0, int kc,
                                             const float *lg, bool plan, bool can_inline, HeadInputs<E> &in,
                                             float known_max, int &n_ex, int &n_ap, int &n_tok, int &inline_limit) {
   constexpr int kBins = bins_of(T);
   constexpr bool kPre = HeadInputs<E>::kPre;
-  constexpr int kGeneralInlineRows = 64;
   const int tid = threadIdx.x;
   const int base = tid * E;
   float(&l)[E] = in.l;
@@ -1005,8 +1014,8 @@ __device__ __forceinline__ bool full_select(const SelectArgs &a, Shared<T> &sh, 
       pa = row16_sum(mine ? sa : 0) + ia - ca;
       pt = row16_sum(mine ? st : 0) + it - te;
     }
-    inline_limit = kGeneralInlineRows;
-    emit.to_lds = can_inline && n_tok + n_ap <= kGeneralInlineRows;
+    inline_limit = general_inline_rows<T>(emit.coherent);
+    emit.to_lds = can_inline && n_tok + n_ap <= inline_limit;
     emit.n_ex = n_ex;
     emit.n_tok = n_tok;
     if (ce + ca > 0) {
