@@ -171,6 +171,19 @@ def test_build_at_block_bin_and_list_edges(clusters, spread):
     check_build(t, gpu_build(t), oracle.build_cluster_cache(t))
 
 
+@pytest.mark.parametrize("longest", [64, 1024, 1025, 4096, 4097, 8192, 8193])
+@pytest.mark.parametrize("clusters", [1, 17, 700])
+def test_build_of_short_segments(longest, clusters):
+    """Segments that a workgroup sorts alone (up to 1024, 4096 and 8192 tokens) and the first length beyond, with tokens
+    that have no valid cluster and a segment without rows.  Bit-exact, as above."""
+    from test_gpu_build import check_build, gpu_build
+    rng = np.random.default_rng(longest + clusters)
+    rows = [longest, 1, max(1, longest // 2), 0, longest - 1, 63]
+    t = _tokens(rows, [clusters] * len(rows), "runs" if clusters == 17 else "uniform", seed=longest)
+    t.assignment[rng.choice(len(t.assignment), max(1, len(t.assignment) // 50), replace=False)] = -1
+    check_build(t, gpu_build(t), oracle.build_cluster_cache(t))
+
+
 def test_build_without_any_cluster_leaves_every_token_out():
     from test_gpu_build import gpu_build
     t = _tokens([5, 4097], [1, 1], "uniform", seed=79)
