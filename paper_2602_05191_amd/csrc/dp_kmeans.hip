@@ -83,7 +83,9 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-template <int TM, bool kQuads>
+// kNorms: the workgroup works out |c|^2 / 2 of the centroids it stages itself (half_norm is not read): the same products
+// and sums in the same order as km_norm_kernel's, so the same bits.
+template <int TM, bool kQuads, bool kNorms = false>
 __device__ __forceinline__ void km_assign(const KmArgs &a) {
   constexpr int kTokensPerWave = 16 * TM, kTokensPerBlock = kTokensPerWave * (kKmThreads / 64);
   __shared__ __attribute__((aligned(16))) char s_c[kKmBufs][kKmCB * kKmRowPad];
@@ -127,14 +129,32 @@ __device__ __forceinline__ void km_assign(const KmArgs &a) {
     const char *src = static_cast<const char *>(a.centroids) + (int64_t)cc * kRowBytes + lq * 64;
 #pragma unroll
     for (int u = 0; u < 4; ++u) x.slice[u] = *reinterpret_cast<const bf16x8 *>(src + 16 * u);
-    x.half_norm = a.half_norm[cc];
+    if (!kNorms) x.half_norm = a.half_norm[cc];
   };
   auto store_block = [&](int buf, int blk, const Staged &x) {
     char *dst = s_c[buf] + lrow * kKmRowPad + lq * 64;
 #pragma unroll
     for (int u = 0; u < 4; ++u) *reinterpret_cast<bf16x8 *>(dst + 16 * u) = x.slice[u];
+    float half_norm;
+    if constexpr (kNorms) {
+      float part[4];  // of 8 dimensions each: a lane of the norm kernel's 16; then the order of its row sum
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float f[8];
+        unpack8(__builtin_bit_cast(uint4, x.slice[u]), f);
+        part[u] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) part[u] = fmaf(f[i], f[i], part[u]);
+      }
+      float sum = (part[0] + part[1]) + (part[2] + part[3]);
+      sum += dpp_mov<0xB1>(sum);  // the neighbouring quarter of the row, then the other half
+      sum += dpp_mov<0x4E>(sum);
+      half_norm = 0.5f * sum;
+    } else {
+      half_norm = x.half_norm;
+    }
     // past the segment's centroids: rows that can never win (a finite product - inf, or NaN: neither is > best)
-    if (lq == 0) s_hn[buf][lrow] = blk * kKmCB + lrow < kc ? -x.half_norm : -INFINITY;
+    if (lq == 0) s_hn[buf][lrow] = blk * kKmCB + lrow < kc ? -half_norm : -INFINITY;
   };
   const char *const my_slices = s_c[0] + r * kKmRowPad + kq * 16;
   const f32x4 *const my_starts = reinterpret_cast<const f32x4 *>(s_hn[0]) + kq;
@@ -303,6 +323,8 @@ __device__ __forceinline__ void km_assign(const KmArgs &a) {
 __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void km_assign8_kernel(KmArgs a) { km_assign<8, true>(a); }
 __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void km_assign4_kernel(KmArgs a) { km_assign<4, false>(a); }
 __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void km_assign2_kernel(KmArgs a) { km_assign<2, false>(a); }
+__global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void km_assign4_norms_kernel(KmArgs a) { km_assign<4, false, true>(a); }
+__global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void km_assign2_norms_kernel(KmArgs a) { km_assign<2, false, true>(a); }
 
 // One 16-lane row copies one key row: centroid c of the segment starts as the key of token floor(c * n / kc).
 __global__ __launch_bounds__(256) void km_init_strided_kernel(KmArgs a, void *centroids) {
@@ -343,8 +365,6 @@ hipError_t launch_kmeans_assign(const KmeansProblem &p, float *half_norm, hipStr
   a.best_score = p.best_score;
   a.max_rows = p.max_rows;
   a.total_clusters = p.total_clusters;
-  if (p.total_clusters > 0)
-    hipLaunchKernelGGL(km_norm_kernel, dim3((p.total_clusters + 15) / 16), dim3(256), 0, s, a);
   // Tokens per workgroup.  128 per wave need the fewest operand bytes per product and the fewest instructions per score,
   // but end with 14 us in which every token's last four candidates are scored again.  Against 64 per wave, where the
   // launch fills the chip at its two workgroups per CU (us):
@@ -363,10 +383,24 @@ hipError_t launch_kmeans_assign(const KmeansProblem &p, float *half_norm, hipStr
     return dim3((p.max_rows + per_block - 1) / per_block, p.n_seg);
   };
   auto blocks = [&](int tm) { return (int64_t)grid(tm).x * grid(tm).y; };
-  if (p.total_clusters / p.n_seg >= 1536 && blocks(8) >= 2 * kKmCus)
+  const bool wide = p.total_clusters / p.n_seg >= 1536 && blocks(8) >= 2 * kKmCus, narrow = !wide && blocks(2) <= 3 * kKmCus;
+  // The norms: by a launch in front (5 us with the gap), or by every workgroup for the centroids it stages, which costs each
+  // 70 instructions per wave and block of 64 centroids.  That pays up to 16 blocks in a row and 16384 in the launch.  Fits of
+  // 3 rounds, us, norms by the workgroups / by a launch: one segment of 2048 x 128 66.4 / 72.7, 24 of up to 7000 x 218 146 / 157,
+  // 128 of up to 2300 x 143 129 / 137, 8 of 8100 x 506 124.5 / 134, 8 of 16384 x 1024 210 / 214; 128 of up to 8000 x 500 385 / 387,
+  // one of 32768 x 2048 200 / 196, two of 65536 x 2048 348 / 336.
+  const int64_t n_blocks = (p.total_clusters / p.n_seg + kKmCB - 1) / kKmCB;
+  const bool own_norms = !wide && n_blocks <= 16 && blocks(narrow ? 2 : 4) * n_blocks <= 16384;
+  if (p.total_clusters > 0 && !own_norms)
+    hipLaunchKernelGGL(km_norm_kernel, dim3((p.total_clusters + 15) / 16), dim3(256), 0, s, a);
+  if (wide)
     hipLaunchKernelGGL(km_assign8_kernel, grid(8), dim3(kKmThreads), 0, s, a);
-  else if (blocks(2) <= 3 * kKmCus)
+  else if (narrow && own_norms)
+    hipLaunchKernelGGL(km_assign2_norms_kernel, grid(2), dim3(kKmThreads), 0, s, a);
+  else if (narrow)
     hipLaunchKernelGGL(km_assign2_kernel, grid(2), dim3(kKmThreads), 0, s, a);
+  else if (own_norms)
+    hipLaunchKernelGGL(km_assign4_norms_kernel, grid(4), dim3(kKmThreads), 0, s, a);
   else
     hipLaunchKernelGGL(km_assign4_kernel, grid(4), dim3(kKmThreads), 0, s, a);
   return hipGetLastError();

@@ -281,3 +281,31 @@ def test_kmeans_assign_same_bits_whatever_the_launch(last):
         one, one_score = assign([s])
         at = slice(int(base[s]), int(base[s + 1]))
         assert torch.equal(asg[at], one[at]) and torch.equal(score[at], one_score[at]), f"segment {s}"
+
+
+@pytest.mark.parametrize("rows", [100, 20000])
+@pytest.mark.parametrize("clusters", [1, 63, 64, 65, 1024, 1025])
+def test_kmeans_assign_same_bits_whoever_works_out_the_norms(rows, clusters):
+    """A segment by itself (up to 1024 centroids: every workgroup takes the norms of the centroids it stages) and beside
+    one with so many centroids that a launch in front does; a centroid with a NaN, one with an infinity, one of zeros."""
+    import torch
+    import paper_2602_05191_amd as dp
+    g = torch.Generator().manual_seed(92)
+    keys = torch.randn(rows + 10, 128, generator=g).bfloat16().cuda()
+    cent = (torch.randn(clusters + 9000, 128, generator=g) * 3).bfloat16()
+    if clusters > 60:
+        cent[5, 3], cent[6, 127], cent[7] = float("nan"), float("inf"), 0.0
+    cent = cent.cuda()
+    got = []
+    for segs in (1, 2):
+        dev = lambda a, dt: torch.from_numpy(np.asarray(a, dt)[:segs + (len(a) == 3)]).cuda()
+        pf = dp.Prefill(keys, keys, torch.zeros(len(keys), dtype=torch.int32, device="cuda"), dev([0, rows], np.int64),
+                        dev([rows, 10], np.int32), dev([0, clusters, clusters + 9000], np.int32),
+                        clusters + 9000 * (segs - 1), 9000 if segs == 2 else clusters, rows)
+        ws = torch.empty(max(dp.dp_kmeans_workspace_bytes(pf), 256), dtype=torch.uint8, device="cuda")
+        asg = torch.full((len(keys),), -7, dtype=torch.int32, device="cuda")
+        score = torch.full((len(keys),), -7.0, device="cuda")
+        dp.dp_kmeans_assign(pf, cent, asg, ws, best_score=score)
+        torch.cuda.synchronize()
+        got.append((asg[:rows], score[:rows]))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
