@@ -177,11 +177,10 @@ dp_status select_only(const dp_problem *problem, const float *logits, const dp::
 
 // Whether a step runs the split decode inside the selection launch.
 // Where the shared launch pays (measured, 32 heads, us per step against three launches): it saves the decode launch
-// of a step whose heads are all attended inline (8192 clusters per KV head: 13.3 against 14.7; 2048 clusters: 12.0
-// against 14.9), and it starts the queue without a launch in between when only some heads are flat (one flat head
-// in eight: 30.3 against 31.8 at 2048 clusters, 50.5 against 55.9 at 8192).  A step of flat heads only is served
-// more slowly by the selection kernel's few large workgroups than by the decode kernel's many small ones (2048
-// clusters: 46 against 43; 8192: 93 against 84): the flag below is for a caller who knows.  With more heads than
+// of a step whose heads are all attended inline (8192 clusters per KV head: 13.5 against 15.2; 2048 clusters: 10.9
+// against 13.8), and it starts the queue without a launch in between when heads are flat (8192 clusters: one flat head
+// in eight 41.0 against 44.5, all of them 64.5 against 67.0; 2048 clusters: 28.3 against 27.5 and 41.1 against 41.1,
+// about level, so the peaked step decides there).  The flag below is for a caller who knows better.  With more heads than
 // kSameLaunchMaxHeads the selecting workgroups come in rounds and the shared launch loses (512 peaked heads: 29.6
 // against 24.3).  Top-p rule only (a fixed budget leaves rows on every head).
 bool shares_launch(const dp_problem *problem, bool by_count) {
