@@ -148,10 +148,13 @@ __device__ __forceinline__ UnitRows unit_rows(int lane, const UnitLists &li, con
   int k = __popc(lo & upto_lo) + __popc(hi & upto_hi);
   int source = __shfl(li.source, k, 64), start = __shfl(li.start, k, 64);
   if (check) {
-    // lists given by a caller: an entry without rows (not allowed, but harmless so far) shares its start with the next
-    // one, and the count is off: look the rows up one by one
+    // lists given by a caller: an entry without rows (not allowed, and it adds nothing) shares its start with the next
+    // one, and the count is off: look the rows up one by one.  The entry behind the last lane's is none of the 64: its
+    // start is read where it matters, behind 63 tokens of one-row clusters.
     const int next = __shfl_down(li.start, 1, 64);
-    if (__any(lane < 63 && ent0 + lane + 1 < n_rt && next == li.start)) {
+    bool empty = lane < 63 && ent0 + lane + 1 < n_rt && next == li.start;
+    if (lane == 63 && d < kChunkRows && ent0 + 63 < n_ex) empty = row_start[ent0 + 64] == li.start;
+    if (__any(empty)) {
       k = 0;
       while (ent0 + k + 1 < n_rt && row_start[ent0 + k + 1] <= row) ++k;
       source = ent_src[ent0 + k];

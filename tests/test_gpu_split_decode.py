@@ -89,3 +89,13 @@ def test_split_decode_of_sets_with_an_empty_cluster():
     c.cluster_sizes[empty] = 0
     approx = [np.array([a for a in ap if a not in empty], dtype=np.int64) for ap in approx]
     _check_sets(c, exact, approx)
+
+
+@pytest.mark.parametrize("at", [62, 63, 64])
+def test_split_decode_of_sets_with_an_empty_cluster_behind_one_row_ones(at):
+    """A wave looks 64 list entries up at a time: one-row clusters up to where the 64 end, then one without rows."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=2, context=1200, mean_cluster=6, size_hi=16, q_scale=0.4, seed=105)
+    n = int(c.seg_cluster_ptr[1])
+    c.cluster_sizes[:at] = np.minimum(c.cluster_sizes[:at], 1)
+    c.cluster_sizes[at] = 0
+    _check_sets(c, [np.arange(n - 20)] * 2, [np.arange(n - 20, n)] * 2)
