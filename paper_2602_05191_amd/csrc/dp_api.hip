@@ -50,6 +50,7 @@ dp::CacheView view_of(const dp_problem *p) {
   c.cluster_flags = p->cluster_flags;
   c.max_clusters_per_seg = p->max_clusters_per_seg;
   c.max_rows_per_seg = p->max_rows_per_seg;
+  c.total_clusters = p->total_clusters;
   // every segment holds <= max clusters and they sum to total: equality means all are full
   const int64_t n_seg = (int64_t)p->batch * p->n_kv_heads;
   c.uniform_kc = (p->max_clusters_per_seg > 0 && n_seg * p->max_clusters_per_seg == p->total_clusters)

@@ -315,15 +315,23 @@ hipError_t launch_score(const CacheView &c, float *logits, hipStream_t s, hipEve
   if (c.group <= kScoreValuMaxGroup) {
     // one pass: 4, 2 or 1 heads at a time
     const dim3 vgrid((c.max_clusters_per_seg + kScoreTile - 1) / kScoreTile, c.batch * c.n_kv_heads);
-    // Whether the centroids are read with non-temporal loads.  They are for launches that read 1.5 to 24 MiB of them, where
-    // a step's layers come from memory anyway and a plain stream is in the way of the next kernel's reads: 8 x 2048
-    // clusters 11.3 -> 10.6 us per step (32 layers), 8 x 8192 14.3 -> 13.5 (12 layers; one layer again and again 13.2 ->
-    // 12.6).  Below, a launch is all latency (256 clusters: 9.0 against 9.2).  Above, a single layer that is scored again
-    // and again (128 segments of 500 to 2000 clusters, 33 MB: about what the L2s hold) loses 0.4 us of 21.4, while six
-    // such layers in turn would gain (23.9 -> 22.3); that the host cannot tell.  (On steps of flat heads, which read
-    // centroids again as pseudo-tokens, it costs 1 %.)
-    const int64_t bytes = (int64_t)c.max_clusters_per_seg * c.batch * c.n_kv_heads * kRowBytes;
-    const bool stream = bytes >= (3 << 19) && bytes <= (24 << 20);
+    // Whether the centroids are read with non-temporal loads: where they are 4 to 24 MiB and one pass reads them.  Steps of
+    // peaked heads, plain / non-temporal loads, us; "cold": 4 layers, and between any two the caches are filled with other
+    // data, as a model's weights do; "warm": one layer's step straight after the other's.
+    //             cold, G = 1     G = 2          G = 4          warm, G = 4
+    //    2 MiB    42.7 / 42.2     44.6 / 43.4    44.3 / 44.0    320.0 / 321.4 (32 layers)
+    //    4 MiB    44.8 / 43.1     44.7 / 41.8    46.0 / 44.6    326.4 / 326.8
+    //    8 MiB    51.3 / 47.1     52.8 / 48.2    54.9 / 51.2    383.6 / 365.6
+    //   16 MiB    57.6 / 53.1     58.4 / 55.5    61.0 / 60.0    457.9 / 427.9
+    //   32 MiB    72.8 / 65.4     73.3 / 66.9    78.7 / 75.1    135.9 / 131.9 (8 layers)
+    // Below 4 MiB, batches of ragged sequences lose warm what they gain cold (5 of 9 k tokens, 3.4 MiB: 50.4 / 50.8 and
+    // 59.4 / 58.0; 8 of 7 k, 2.1 MiB: 39.9 / 40.4 and 47.1 / 47.2).  Above 24 MiB, one layer that is scored again and again
+    // out of the caches loses (32 MiB, G = 1: 12.3 / 12.95), which the host cannot tell from a step's layers.  A group that
+    // takes two passes (G = 3) reads its centroids again at once: warm 16 MiB 64.5 / 67.0 and 32 MiB 79.5 / 86.8 over 4
+    // layers, with only the last pass non-temporal no gain either (cold 75.5 / 75.6).  (Flat heads read centroids again as
+    // pseudo-tokens and lose up to 1.5 %: 16 MiB, 2 layers cold 164.2 / 166.6.)
+    const int64_t bytes = (int64_t)c.total_clusters * kRowBytes;
+    const bool stream = c.group != 3 && bytes >= (4 << 20) && bytes <= (24 << 20);
     int h0 = 0;
     while (h0 < c.group) {
       const int left = c.group - h0, gh = left >= 4 ? 4 : left >= 2 ? 2 : 1;
