@@ -64,6 +64,7 @@ struct SelectArgs {
   float p1, p2;
   uint32_t p2_absolute;
   int32_t k_retained, k_exact;  // fixed-budget rule (the kernel's kCount variant): counts instead of p1, p2
+  int32_t general_inline;       // most rows a head's own workgroup attends after the general search (<= inline_rows_of(T))
   SelectOut out;
   Plan plan;
   // inline attention (one-call path); out == nullptr disables it
@@ -753,22 +754,32 @@ __device__ __forceinline__ void load_head_inputs(const SelectArgs &a, int c0, in
   }
 }
 
-// Rows of a head that its own workgroup attends although the search has taken its time already.  With the queue in this
-// launch (`gate`) a list costs some 10 us there until it is merged (every head has to report first), as much as the
-// workgroup needs for all the rows its lists hold: 128 flat heads over 4.5 k tokens 27.7 -> 25.3 us per step, 4 heads over
-// 4.5 k, two of them flat, 19.2 -> 16.9.  With a decode launch behind this one, a head per CU: 256 (a budget of 2 heads
-// over 4.5 k tokens 17.6 -> 15.9: nothing is left for that launch).  More heads than that come in rounds, and what holds
-// up a round costs more than it saves (256 heads over 11 k tokens, half of them flat: 39.8 at 64 and 128 rows, 41.2 at 256).
-template <int T>
-__device__ __forceinline__ int general_inline_rows(bool gate) {
-  return gate ? inline_rows_of(T) : gridDim.x <= 128 ? 256 : 64;
-}
+// Rows of a head that its own workgroup attends although the general search has taken its time already (a head that took
+// the fast path is attended up to what the LDS lists hold).
+//   The queue in this launch: 512.  A list costs some 10 us there until it is merged (every head has to report first), as
+// much as the workgroup needs for the rows.  128 flat heads over 4.5 k tokens, four layers, limits of 64 / 256 / 512 rows:
+// 129.9 / 127.8 / 123.1 us; 32 heads over 5000 clusters, the flattest with 171 tokens on average, two layers: 57.1 / 52.4 /
+// 50.8.  1024 rows are more than a workgroup of 1024 threads attends in that time (heads of up to 955 rows over 8192
+// clusters, two layers: 53.8 at 512, 56.3 at 1024; 128 heads of up to 668 rows over 5000: 70.0 and 73.3).
+//   A decode launch behind this one: attending a few heads here costs 1 to 5 us and saves nothing, attending all of them
+// leaves that launch without work and saves 3 to 7.  So 64 rows, one round of loads for four waves (two thresholds, 128
+// heads over 11 k tokens, half of them flat: 29.4 us, at 256 rows 31.6), and 256 where the heads of a fixed budget will
+// hold no more: its approximated clusters and twice the mean size of its exact ones, because the sizes that k-means leaves
+// vary by as much as their mean (0.7 to 1.0 of it).  Limits of 64 / 256 rows, sizes varying by 0.9, budgets of 2 exact
+// clusters of 50, 3 of 80 and 4 of 90, inside the line: 16 heads 23.4 / 17.1, 21.3 / 18.1, 21.2 / 18.5; 32 heads over 2048
+// clusters 24.4 / 18.7, 22.2 / 19.4, 22.2 / 21.5; 128 heads 26.5 / 20.7, 25.7 / 21.5, 25.8 / 22.5 (over 8192 clusters only
+// the first gains, 40.3 / 34.9, then 38.8 / 42.2).  On it and outside, 6 of 70, 6 of 100 and 4 of 160: 32 heads 22.1 / 26.6,
+// 22.4 / 26.9 and 22.6 / 26.9, 128 heads 26.0 / 28.7, 26.4 / 29.4 and 27.2 / 29.8.  (Even sizes gain up to 6 of 140 as well, 22.4 / 19.6; a long tail, with clusters
+// over the limit themselves, loses inside the line too where heads are many: 2 of 50, 128 heads, 26.8 / 28.2.)  More than
+// 128 heads, even sizes and a long tail: 256 heads, 2 of 50, 25.7 / 18.2 and 25.9 / 26.8; those keep 64.
+constexpr int kInlineQueue = 512, kInlineBudget = 256, kInlineGeneral = 64;
+static_assert(kInlineBudget <= inline_rows_of(256) && kInlineQueue <= inline_rows_of(512), "the lists of the smallest workgroups");
 
 // The selection proper for one head (one workgroup) on the thread's loaded inputs: fast path for a peaked head,
 // general threshold search otherwise; emits the lists (and the plan) and returns the three counts.  Returns false
 // when the head had no candidate at all and has been finished here (counts, zero output).  known_max: the head's max
 // logit if the caller has it already (NaN if not).  inline_limit: the most rows of this head that are worth
-// attending in this workgroup (general_inline_rows below for a head that took the general path).
+// attending in this workgroup (kInlineQueue or a.general_inline for a head that took the general path).
 template <int E, bool kCount, int T>
 __device__ __forceinline__ bool full_select(const SelectArgs &a, Shared<T> &sh, Emit &emit, int head, int c0, int kc,
                                             const float *lg, bool plan, bool can_inline, HeadInputs<E> &in,
@@ -1014,7 +1025,7 @@ __device__ __forceinline__ bool full_select(const SelectArgs &a, Shared<T> &sh, 
       pa = row16_sum(mine ? sa : 0) + ia - ca;
       pt = row16_sum(mine ? st : 0) + it - te;
     }
-    inline_limit = general_inline_rows<T>(emit.coherent);
+    inline_limit = emit.coherent ? kInlineQueue : kCount ? a.general_inline : kInlineGeneral;
     emit.to_lds = can_inline && n_tok + n_ap <= inline_limit;
     emit.n_ex = n_ex;
     emit.n_tok = n_tok;
@@ -1392,6 +1403,13 @@ void launch_select_e(const SelectArgs &a, bool by_count, dim3 grid, hipStream_t 
   }
 }
 
+int general_inline_of(const CacheView &c, const SelectRule &rule) {
+  const int64_t mk = c.max_clusters_per_seg;
+  if (!rule.by_count || mk == 0 || (int64_t)c.batch * c.n_q_heads > 128) return kInlineGeneral;
+  const int64_t kept = rule.k_retained < mk ? rule.k_retained : mk, exact = rule.k_exact < kept ? rule.k_exact : kept;
+  return kept - exact + 2 * exact * c.max_rows_per_seg / mk < kInlineBudget ? kInlineBudget : kInlineGeneral;
+}
+
 }  // namespace
 
 
@@ -1416,6 +1434,7 @@ hipError_t launch_select(const CacheView &c, const float *logits, const SelectRu
   a.p2_absolute = rule.p2_absolute;
   a.k_retained = rule.k_retained;
   a.k_exact = rule.k_exact;
+  a.general_inline = general_inline_of(c, rule);
   const bool bc = rule.by_count != 0;
   a.out = out;
   a.plan = plan;

@@ -99,3 +99,26 @@ def test_split_decode_of_sets_with_an_empty_cluster_behind_one_row_ones(at):
     c.cluster_sizes[:at] = np.minimum(c.cluster_sizes[:at], 1)
     c.cluster_sizes[at] = 0
     _check_sets(c, [np.arange(n - 20)] * 2, [np.arange(n - 20, n)] * 2)
+
+
+@pytest.mark.parametrize("batch", [1, 33])
+@pytest.mark.parametrize("budget", [(50, 2), (105, 4), (120, 4), (160, 4)])
+def test_budget_heads_around_the_rows_their_own_workgroup_attends(budget, batch):
+    """Launches of few and of many heads, budgets of some 80 to 220 rows: attended with the selection, by the decode
+    launch, or some heads here and some there."""
+    c = make_cache(batch=batch, n_kv_heads=1, n_q_heads=4, context=6000, mean_cluster=16, q_scale=0.4, seed=106)
+    g = H.gpu_decode_attention(c, 0, 0, budget=budget)
+    rows = np.array([t + len(a) for t, a in zip(g.n_exact_tokens, g.approx)])
+    assert rows.min() > 64 and (budget[0] < 150 or rows.max() > 200)
+    H.check_outputs(c, oracle.Oracle(c), g, tight=TIGHT)
+
+
+@pytest.mark.parametrize("p1, fewest, most", [(0.1, 190, 300), (0.15, 330, 512), (0.18, 420, 600), (0.35, 1000, 1400)])
+def test_flat_heads_around_the_rows_their_own_workgroup_attends(p1, fewest, most):
+    """The search of 1024 threads per head (more than 4096 clusters): heads below 512 rows, on both sides, and beyond."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=16, context=9000, mean_cluster=2, size_hi=4, q_scale=0.3, seed=107)
+    assert c.max_clusters_per_seg > 4096
+    g = H.gpu_decode_attention(c, p1, 0.5, sm_scale=0.02)
+    rows = np.array([t + len(a) for t, a in zip(g.n_exact_tokens, g.approx)])
+    assert fewest < rows.min() and rows.max() < most, rows
+    H.check_outputs(c, oracle.Oracle(c, sm_scale=0.02), g, tight=TIGHT)
