@@ -215,7 +215,8 @@ dp_status whole_step(const dp_problem *problem, const dp::SelectRule &rule, void
   // the summaries serve the top-p rule on heads without cluster flags
   float2 *summ = (!rule.by_count && !problem->cluster_flags && rule.p1 < 1.0f) ? w.summaries : nullptr;
   // the scoring kernel clears the step's counters: item counters, pending counters, planned (contiguous), and
-  // in front of them head_rows when the queue runs inside the selection launch (only heads with rows write it then)
+  // in front of them head_rows when the queue runs inside the selection launch (every head reports there, what is not
+  // 0 counts as its report)
   int32_t *zero = !w.plan.pending ? nullptr : same_launch ? w.plan.head_rows : w.plan.queue_next;
   const int n_zero = 2 * n_slabs + 1 + (same_launch ? nh_i : 0);
   if (dp::launch_score(c, w.logits, s, ev[0], ev[1], zero, n_zero, summ, w.sub_stride) != hipSuccess) return DP_ERR_HIP;

@@ -33,7 +33,7 @@ struct CacheView {
 //   row_start[nh, max_k + 1]  exclusive prefix of rows over the entry list
 //                             (an exact cluster has s_i rows, an approximated one has 1)
 //   chunk_entry[nh, chunk_stride]  entry that holds row q*kChunkRows
-//   head_rows[nh]             total rows of the head; -1: the head has already been attended
+//   head_rows[nh]             total rows of the head; -1: nothing is left to attend (0 as well, where no queue waits for it)
 //   done[nh]                  arrival counter of the head's decode workgroups (zeroed by the planner)
 struct Plan {
   int32_t *ent_src, *row_start, *chunk_entry, *head_rows, *done;
@@ -81,8 +81,9 @@ struct SelectRule {
 // With a plan and attn.out != nullptr, heads with few rows are attended inside the selection kernel.
 // The stage-3 queue inside the selection launch (for launches that serve at most kSameLaunchMaxHeads heads):
 // the heads that the selection does not attend itself are split over the same launch's workgroups, so no decode
-// launch follows.  planned: one counter; it, plan.pending[0] and plan.queue_next[0] must be zero when the launch
-// starts (launch_score's zero_words).
+// launch follows.  planned: one counter; it, plan.queue_next[0] and plan.head_rows[0 .. heads) must be zero when the launch
+// starts (launch_score's zero_words).  A workgroup that waits takes a head_rows[head] other than 0 for that head's report
+// (its rows, or -1 for none): a word left by an earlier step would start the queue on lists that are not written yet.
 constexpr int kSameLaunchMaxHeads = 128;
 struct SameLaunchQueue {
   float *partials;

@@ -758,20 +758,21 @@ __device__ __forceinline__ void load_head_inputs(const SelectArgs &a, int c0, in
 // the fast path is attended up to what the LDS lists hold).
 //   The queue in this launch: 512.  A list costs some 10 us there until it is merged (every head has to report first), as
 // much as the workgroup needs for the rows.  128 flat heads over 4.5 k tokens, four layers, limits of 64 / 256 / 512 rows:
-// 129.9 / 127.8 / 123.1 us; 32 heads over 5000 clusters, the flattest with 171 tokens on average, two layers: 57.1 / 52.4 /
-// 50.8.  1024 rows are more than a workgroup of 1024 threads attends in that time (heads of up to 955 rows over 8192
-// clusters, two layers: 53.8 at 512, 56.3 at 1024; 128 heads of up to 668 rows over 5000: 70.0 and 73.3).
+// 129.9 / 127.8 / 123.1 us; 32 heads over 5000 clusters, the flattest of some 200 rows, two layers: 57.1 / 52.4 / 50.8.
+// 1024 rows are more than a workgroup of 1024 threads attends in that time (heads of up to 955 rows over 8192 clusters, two
+// layers: 53.8 at 512, 56.3 at 1024; 128 heads of up to 668 rows over 5000: 70.0 and 73.3).
 //   A decode launch behind this one: attending a few heads here costs 1 to 5 us and saves nothing, attending all of them
 // leaves that launch without work and saves 3 to 7.  So 64 rows, one round of loads for four waves (two thresholds, 128
-// heads over 11 k tokens, half of them flat: 29.4 us, at 256 rows 31.6), and 256 where the heads of a fixed budget will
-// hold no more: its approximated clusters and twice the mean size of its exact ones, because the sizes that k-means leaves
-// vary by as much as their mean (0.7 to 1.0 of it).  Limits of 64 / 256 rows, sizes varying by 0.9, budgets of 2 exact
-// clusters of 50, 3 of 80 and 4 of 90, inside the line: 16 heads 23.4 / 17.1, 21.3 / 18.1, 21.2 / 18.5; 32 heads over 2048
-// clusters 24.4 / 18.7, 22.2 / 19.4, 22.2 / 21.5; 128 heads 26.5 / 20.7, 25.7 / 21.5, 25.8 / 22.5 (over 8192 clusters only
-// the first gains, 40.3 / 34.9, then 38.8 / 42.2).  On it and outside, 6 of 70, 6 of 100 and 4 of 160: 32 heads 22.1 / 26.6,
-// 22.4 / 26.9 and 22.6 / 26.9, 128 heads 26.0 / 28.7, 26.4 / 29.4 and 27.2 / 29.8.  (Even sizes gain up to 6 of 140 as well, 22.4 / 19.6; a long tail, with clusters
-// over the limit themselves, loses inside the line too where heads are many: 2 of 50, 128 heads, 26.8 / 28.2.)  More than
-// 128 heads, even sizes and a long tail: 256 heads, 2 of 50, 25.7 / 18.2 and 25.9 / 26.8; those keep 64.
+// heads over 11 k tokens, half of them flat: 29.4 us, at 256 rows 31.6), and 256 where the heads of a fixed budget will hold
+// no more: its approximated clusters and twice the mean size of its exact ones, because the sizes that k-means leaves vary
+// by as much as their mean (0.7 to 1.0 of it).  Limits of 64 / 256 rows, sizes varying by 0.9, budgets of 2 exact clusters
+// of 50, 3 of 80 and 4 of 90, inside the line: 16 heads 23.4 / 17.1, 21.3 / 18.1, 21.2 / 18.5; 32 heads over 2048 clusters
+// 24.4 / 18.7, 22.2 / 19.4, 22.2 / 21.5; 128 heads 26.5 / 20.7, 25.7 / 21.5, 25.8 / 22.5 (over 8192 clusters only the first
+// gains, 40.3 / 34.9, then 38.8 / 42.2).  On it and outside, 6 of 70, 6 of 100 and 4 of 160: 32 heads 22.1 / 26.6, 22.4 /
+// 26.9 and 22.6 / 26.9, 128 heads 26.0 / 28.7, 26.4 / 29.4 and 27.2 / 29.8.  (Even sizes gain up to 6 of 140 as well, 22.4 /
+// 19.6; a long tail, with clusters over the limit themselves, loses inside the line too: 2 of 50, 128 heads, 26.8 / 28.2; 4
+// of 100, 32 heads, 22.3 / 26.6.)  More than 128 heads keep 64 (256 heads, 2 of 50: even sizes 25.7 / 18.2, a long tail 25.9
+// / 26.8).
 constexpr int kInlineQueue = 512, kInlineBudget = 256, kInlineGeneral = 64;
 static_assert(kInlineBudget <= inline_rows_of(256) && kInlineQueue <= inline_rows_of(512), "the lists of the smallest workgroups");
 
