@@ -38,15 +38,15 @@ struct RowSources {
   int64_t gather_row0;
 };
 
-// Attend rows ra, ra+1, .., ra+B-1, then ra+stride .. (B rows in flight per step), below rb.  s_start[0 .. n_ent] and s_src[0 .. n_ent)
+// Attend rows ra, ra+1, .., ra+B-1, then ra+stride .. (B = kAttendBatch rows in flight per step), below rb.  s_start[0 .. n_ent] and s_src[0 .. n_ent)
 // are the staged row_start / ent_src of entries ent0 .. ent0+n_ent-1, which
 // cover [ra, rb) (s_start[0] <= ra).  Every lane of the group runs the same
 // entry walk (uniform inside the group), so nothing is exchanged between lanes
 // except the DPP sum of the dot product.
-template <bool kGathered = false, int B = kAttendBatch>
 __device__ __forceinline__ void attend_rows(RowState &st, const uint4 &qv, float scale_log2, const RowSources &src,
                                             const int *s_start, const int *s_src, int n_ent, int ent0, int n_ex,
                                             int ra, int rb, int stride, int lane16) {
+  constexpr int B = kAttendBatch;
   if (ra >= rb) return;
   // entry that holds row ra: largest k in [0, n_ent) with s_start[k] <= ra
   int k = 0;
@@ -74,13 +74,8 @@ __device__ __forceinline__ void attend_rows(RowState &st, const uint4 &qv, float
         if (ent0 + k < n_ex) {
           const int64_t g = src.seg_row0 + s + (row - s_start[k]);
           ssz[u] = 1;
-          if (kGathered) {
-            kraw[u] = load_row_slice(src.k_gather, src.gather_row0 + row, lane16);
-            vraw[u] = load_row_slice(src.v_gather, src.gather_row0 + row, lane16);
-          } else {
-            kraw[u] = load_row_slice(src.k_cache, g, lane16);
-            vraw[u] = load_row_slice(src.v_cache, g, lane16);
-          }
+          kraw[u] = load_row_slice(src.k_cache, g, lane16);
+          vraw[u] = load_row_slice(src.v_cache, g, lane16);
         } else {
           ssz[u] = src.seg_sizes[s];
           kraw[u] = load_row_slice(src.k_centroids, src.c0 + s, lane16);

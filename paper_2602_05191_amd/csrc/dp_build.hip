@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void build_place_kernel(BuildArgs a) {
 // rank, scan and place of a segment of at most T * R tokens by one workgroup: the counts stay in LDS and a token's cluster and
 // rank in registers.  Bounded by latency (the ids in, the words out; a few LDS round trips per 64 tokens of a wave): 24
 // segments of 1.2 k to 5 k tokens take 7.2 us, in three launches they took 5.0, 4.1 and 3.0 and the gaps between.
-template <class Word, int T, int R>
+template <int T, int R>
 __global__ __launch_bounds__(T) void build_sort_kernel(BuildArgs a) {
   extern __shared__ uint32_t s_words[];  // 16-bit counts [T / 64][bin_stride], then the starts of the bins
   __shared__ int scr[T / 64 + 1];
@@ -269,12 +269,12 @@ __global__ __launch_bounds__(T) void build_sort_kernel(BuildArgs a) {
     if (a.cluster_sizes) a.cluster_sizes[c0 + i] = 0;
   }
   __syncthreads();
-  Word *out = static_cast<Word *>(a.binned) + (size_t)seg * a.max_rows;
+  uint32_t *out = static_cast<uint32_t *>(a.binned) + (size_t)seg * a.max_rows;
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     if (c[u] < 0) continue;
     const int bin = c[u] >> 4;
-    out[s_start[bin] + mine[bin] + rank[u]] = (Word)(t0 + 64 * u) * kBinClusters + (Word)(c[u] % kBinClusters);
+    out[s_start[bin] + mine[bin] + rank[u]] = (uint32_t)(t0 + 64 * u) * kBinClusters + (uint32_t)(c[u] % kBinClusters);
   }
 }
 
@@ -541,7 +541,7 @@ void move(const BuildArgs &a, int n_seg, hipStream_t s) {
 template <int T, int R>
 void sort_short(const BuildArgs &a, int n_seg, hipStream_t s) {
   const size_t lds = (size_t)a.bin_stride * (T / 64 * sizeof(uint16_t) + sizeof(int));
-  hipLaunchKernelGGL((build_sort_kernel<uint32_t, T, R>), dim3(n_seg), dim3(T), lds, s, a);
+  hipLaunchKernelGGL((build_sort_kernel<T, R>), dim3(n_seg), dim3(T), lds, s, a);
 }
 
 }  // namespace

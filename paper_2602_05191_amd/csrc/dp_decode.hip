@@ -12,10 +12,11 @@ constexpr int kDecThreads = 256;
 template <bool kGathered>
 __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(kGathered ? 4 : 5))) void decode_kernel(const int32_t *pending, DecodeArgs a) {
   DP_DECODE_LDS(kDecThreads, kMaxQueueHeads);
+  __shared__ int s_first[kMaxQueueHeads + 1], s_scan[kDecThreads / 64 + 1];
   // (a leading scalar parameter: it is in a register when the wave starts, so a launch that finds nothing to do
   // issues this load first and fetches no other argument)
   if (pending && *pending == 0) return;  // every head was finished by the selection kernel
-  decode_queue<kDecThreads, kGathered>(a, DP_DECODE_LDS_ARGS);
+  decode_queue<kDecThreads, kGathered>(a, DP_DECODE_LDS_ARGS, s_first, s_scan);
 }
 
 }  // namespace

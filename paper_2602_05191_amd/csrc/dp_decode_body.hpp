@@ -119,10 +119,8 @@ __device__ __forceinline__ int rows_per_item(int R, int S, int g) {
   __shared__ float s_m[(T) / 64], s_l[(T) / 64];                                                   \
   __shared__ float s_acc[(T) / 64][kHeadDim];                                                      \
   __shared__ int s_last, s_item;                                                                   \
-  __shared__ int s_first[(HEADS) + 1]; /* first item number of each head of this launch */         \
-  __shared__ int s_scan[(T) / 64 + 1];                                                             \
   __shared__ int s_rows[(HEADS)]
-#define DP_DECODE_LDS_ARGS s_m, s_l, s_acc, &s_last, &s_item, s_first, s_scan, s_rows
+#define DP_DECODE_LDS_ARGS s_m, s_l, s_acc, &s_last, &s_item, s_rows
 
 // What the rows [r0, r1) of a head's list are, one row per lane: lane 16 g + j takes row j of group g, `per` rows per
 // group (4 per <= 64 rows, inside one 64-row chunk of the list whose first row lies in entry ent0).  Lane k holds the
@@ -331,9 +329,10 @@ __device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int s
 
 // The queue of a decode launch: the plan was written by an earlier launch.  A workgroup's first item is its block index,
 // further items are claimed from the counter.  Call with the whole workgroup.
+// s_first [kMaxQueueHeads + 1]: first item number of each head of this launch; s_scan [T / 64 + 1].
 template <int T, bool kGathered>
 __device__ __forceinline__ void decode_queue(const DecodeArgs &a, float *s_m, float *s_l, float (*s_acc)[kHeadDim],
-                                             int *s_last, int *s_item, int *s_first, int *s_scan, int *s_rows) {
+                                             int *s_last, int *s_item, int *s_rows, int *s_first, int *s_scan) {
   const int tid = threadIdx.x;
 
   // ---- the queue: items per head from head_rows[], exclusive prefix in LDS ----
@@ -409,7 +408,7 @@ __device__ __forceinline__ void decode_queue(const DecodeArgs &a, float *s_m, fl
 // for 240 MB.)
 template <int T>
 __device__ __forceinline__ void decode_queue_here(const DecodeArgs &a, int first, float *s_m, float *s_l, float (*s_acc)[kHeadDim],
-                                                  int *s_last, int *s_item, int *s_first, int *s_scan, int *s_rows) {
+                                                  int *s_last, int *s_item, int *s_rows) {
   static_assert(kSameLaunchMaxHeads == 128, "two heads per lane");
   const int tid = threadIdx.x, lane = lane_id();
   // every wave works the cut out for itself

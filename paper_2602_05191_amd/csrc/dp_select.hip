@@ -1233,7 +1233,7 @@ struct QueueArgs {  // what the stage-3 queue needs beyond the selection's own a
   int32_t *planned;
   int32_t splits, n_heads;
 };
-template <int E, bool kCount, int T>
+template <int E, int T>
 __global__ __launch_bounds__(T) void select_decode_kernel(SelectArgs a, QueueArgs qa) {
   __shared__ Shared<T> sh;
   DP_DECODE_LDS(T, kSameLaunchMaxHeads);
@@ -1242,7 +1242,7 @@ __global__ __launch_bounds__(T) void select_decode_kernel(SelectArgs a, QueueArg
   const int n_heads = qa.n_heads;
   int word = -1;
   const bool selects = (int)blockIdx.x < n_heads;
-  if (selects) word = select_head<E, kCount, T, true>(a, sh, planned);
+  if (selects) word = select_head<E, false, T, true>(a, sh, planned);
   int first = 0;
   if (threadIdx.x >= T - 64) {  // the last wave decides
     const int lane = lane_id();
@@ -1373,24 +1373,21 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
   if (R == 0 && a.attn_out && tid < kHeadDim) store_out(a.attn_out, a.out_is_bf16, head, tid, 0.f);
 }
 
-// with a queue: more workgroups than heads
+// with a queue: more workgroups than heads (top-p rule only, and heads too few for the smallest workgroups)
 template <int E, int T>
 void launch_select_e(const SelectArgs &a, bool by_count, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop,
                      const QueueArgs *queue) {
   if (queue) {
-    // one workgroup per CU: more of them help a heavy queue no more (512 workgroups of 512 threads: 3 ragged sequences of
+    // One workgroup per CU: more of them help a heavy queue no more (512 workgroups of 512 threads: 3 ragged sequences of
     // up to 38 k tokens with a flat head in eight 147 us per four layers against 130), and a workgroup that has to wait
-    // for a place would only find the count complete and leave, at the launch's expense
-    const dim3 g(grid.x + 32 > 256u ? grid.x + 32 : 256u);
-    if (start || stop) {
-      if (by_count)
-        hipExtLaunchKernelGGL((select_decode_kernel<E, true, T>), g, dim3(T), 0, s, start, stop, 0, a, *queue);
+    // for a place would only find every head reported and leave, at the launch's expense.
+    if constexpr (T >= kSelThreads / 2) {
+      constexpr unsigned kCus = 256;
+      static_assert(kCus >= 2 * kSameLaunchMaxHeads, "every head has its workgroup, and as many serve from the start");
+      if (start || stop)
+        hipExtLaunchKernelGGL((select_decode_kernel<E, T>), dim3(kCus), dim3(T), 0, s, start, stop, 0, a, *queue);
       else
-        hipExtLaunchKernelGGL((select_decode_kernel<E, false, T>), g, dim3(T), 0, s, start, stop, 0, a, *queue);
-    } else if (by_count) {
-      hipLaunchKernelGGL((select_decode_kernel<E, true, T>), g, dim3(T), 0, s, a, *queue);
-    } else {
-      hipLaunchKernelGGL((select_decode_kernel<E, false, T>), g, dim3(T), 0, s, a, *queue);
+        hipLaunchKernelGGL((select_decode_kernel<E, T>), dim3(kCus), dim3(T), 0, s, a, *queue);
     }
   } else if (start || stop) {  // measurement: the runtime stamps the kernel's own begin and end
     if (by_count)
@@ -1455,7 +1452,7 @@ hipError_t launch_select(const CacheView &c, const float *logits, const SelectRu
   QueueArgs qa;
   const QueueArgs *q = nullptr;
   if (queue) {
-    if (grid.x > (unsigned)kSameLaunchMaxHeads || !plan.ent_src || !attn.out) return hipErrorInvalidValue;
+    if (grid.x > (unsigned)kSameLaunchMaxHeads || bc || !plan.ent_src || !attn.out) return hipErrorInvalidValue;
     qa = QueueArgs{queue->partials, queue->planned, queue->splits, (int32_t)grid.x};
     q = &qa;
   }
