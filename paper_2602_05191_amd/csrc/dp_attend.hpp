@@ -33,8 +33,7 @@ struct RowSources {
   const int32_t *seg_sizes;  // cluster_sizes + c0 of the head's segment
   int64_t seg_row0;          // first cache row of the segment
   int64_t c0;                // first centroid row of the segment
-  // A/B variant only (kGathered): the head's exact rows copied to a contiguous buffer, list row r at gather_row0 + r
-  const void *k_gather, *v_gather;
+  // A/B variant only (kGathered), >= 0: k_cache / v_cache are a buffer with the head's exact rows, list row r at gather_row0 + r
   int64_t gather_row0;
 };
 

@@ -10,7 +10,7 @@ namespace {
 constexpr int kDecThreads = 256;
 
 template <bool kGathered>
-__global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(kGathered ? 4 : 5))) void decode_kernel(const int32_t *pending, DecodeArgs a) {
+__global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(5))) void decode_kernel(const int32_t *pending, DecodeArgs a) {
   DP_DECODE_LDS(kDecThreads, kMaxQueueHeads);
   __shared__ int s_first[kMaxQueueHeads + 1], s_scan[kDecThreads / 64 + 1];
   // (a leading scalar parameter: it is in a register when the wave starts, so a launch that finds nothing to do

@@ -163,16 +163,10 @@ __device__ __forceinline__ UnitRows unit_rows(int lane, const UnitLists &li, con
   // (unconditional, and an atomic load so that it stays so: inside a condition it is waited for on its own)
   const int size = __hip_atomic_load(src.seg_sizes + (exact ? 0 : source), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   UnitRows u;
-  uint64_t ka, va;
-  if (kGathered && src.k_gather) {
-    const int64_t g = exact ? src.gather_row0 + row : src.c0 + source;
-    ka = (uint64_t)(exact ? src.k_gather : src.k_centroids) + g * kRowBytes;
-    va = (uint64_t)(exact ? src.v_gather : src.v_centroids) + g * kRowBytes;
-  } else {
-    const int64_t g = exact ? src.seg_row0 + source + (row - start) : src.c0 + source;
-    ka = (uint64_t)(exact ? src.k_cache : src.k_centroids) + g * kRowBytes;
-    va = (uint64_t)(exact ? src.v_cache : src.v_centroids) + g * kRowBytes;
-  }
+  const int64_t token = kGathered && src.gather_row0 >= 0 ? src.gather_row0 + row : src.seg_row0 + source + (row - start);
+  const int64_t g = exact ? token : src.c0 + source;
+  const uint64_t ka = (uint64_t)(exact ? src.k_cache : src.k_centroids) + g * kRowBytes;
+  const uint64_t va = (uint64_t)(exact ? src.v_cache : src.v_centroids) + g * kRowBytes;
   u.klo = (uint32_t)ka;
   u.khi = (uint32_t)(ka >> 32);
   u.vlo = (uint32_t)va;
@@ -242,12 +236,11 @@ __device__ __forceinline__ void decode_item(const DecodeArgs &a, int head, int s
   src.seg_sizes = a.cluster_sizes + c0;
   src.seg_row0 = a.seg_row_base[seg];
   src.c0 = c0;
-  src.k_gather = src.v_gather = nullptr;
-  src.gather_row0 = 0;
+  src.gather_row0 = -1;
   // a head whose exact rows did not fit the buffer was not gathered: it is read in place
   if (kGathered && n_ex > 0 && row_start[n_ex] <= a.rows_cap) {
-    src.k_gather = a.k_gather;
-    src.v_gather = a.v_gather;
+    src.k_cache = a.k_gather;
+    src.v_cache = a.v_gather;
     src.gather_row0 = (int64_t)head * a.rows_cap;
   }
 

@@ -217,8 +217,6 @@ __global__ __launch_bounds__(kGrpThreads) void group_decode_kernel(GroupArgs a) 
   src.seg_sizes = a.cluster_sizes + c0;
   src.seg_row0 = a.seg_row_base[seg];
   src.c0 = c0;
-  src.k_gather = src.v_gather = nullptr;
-  src.gather_row0 = 0;
 
   RowState st[GH];
 #pragma unroll
