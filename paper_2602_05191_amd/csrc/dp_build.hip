@@ -65,6 +65,68 @@ __device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOM
 
 __device__ __forceinline__ uint64_t lanes_below() { return (1ull << lane_id()) - 1; }
 
+// ---- shared by the sort in three launches and the one in a single one ----
+
+// a thread's tokens t0, t0 + 64, ..: their clusters, -1 for a token without a valid one
+template <int R>
+__device__ __forceinline__ void leave_out_invalid(const BuildArgs &a, int (&c)[R], int t0, int n, int kc, int64_t r0) {
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    const int t = t0 + 64 * u;
+    if (t >= n || (unsigned)c[u] >= (unsigned)kc) {
+      c[u] = -1;
+      if (a.token_row && t < n) a.token_row[r0 + t] = -1;
+    }
+  }
+}
+
+// rank of each token among the wave's earlier tokens of its bin; mine: the wave's counts per bin, 0 so far
+template <int R>
+__device__ __forceinline__ void rank_in_bins(const int (&c)[R], int (&rank)[R], uint16_t *mine, int n_bins) {
+  const int bits = n_bins > 1 ? 32 - __clz(n_bins - 1) : 0;
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    const int bin = c[u] >> 4;
+    const bool live = c[u] >= 0;
+    uint64_t peers = __ballot(live);
+    rank[u] = 0;
+    if (peers == 0) continue;
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = (bin >> b) & 1;
+      const uint64_t ones = __ballot(bit);
+      peers &= bit ? ones : ~ones;
+    }
+    const int before = live ? mine[bin] : 0;
+    const int ahead = __popcll(peers & lanes_below());
+    rank[u] = before + ahead;
+    wave_lds_order();
+    if (live && ahead == 0) mine[bin] = (uint16_t)(before + __popcll(peers));
+    wave_lds_order();
+  }
+}
+
+// exclusive prefix of a bin's counts over the waves, in place; returns their sum
+template <int W>
+__device__ __forceinline__ int prefix_over_waves(uint16_t *bin, int stride) {
+  int run = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const int v = bin[w * stride];
+    bin[w * stride] = (uint16_t)run;
+    run += v;
+  }
+  return run;
+}
+
+// clusters beyond the host's bound received no token: they are reported empty
+template <int T>
+__device__ __forceinline__ void report_unbounded_empty(const BuildArgs &a, int c0, int kc_all, int n_placed, int tid) {
+  for (int i = a.max_kc + tid; i < kc_all; i += T) {
+    if (a.cluster_offsets) a.cluster_offsets[c0 + i] = n_placed;
+    if (a.cluster_sizes) a.cluster_sizes[c0 + i] = 0;
+  }
+}
+
 __global__ __launch_bounds__(kRankThreads) void build_rank_kernel(BuildArgs a) {
   extern __shared__ uint32_t s_words[];  // 16-bit counts [kRankWaves][bin_stride]
   uint16_t *const tab = reinterpret_cast<uint16_t *>(s_words);
@@ -79,48 +141,15 @@ __global__ __launch_bounds__(kRankThreads) void build_rank_kernel(BuildArgs a) {
 #pragma unroll
   for (int u = 0; u < kRankRounds; ++u) c[u] = a.assignment[r0 + min(t0 + 64 * u, n - 1)];
   for (int i = tid; i < kRankWaves * a.bin_stride / 2; i += kRankThreads) s_words[i] = 0;
-#pragma unroll
-  for (int u = 0; u < kRankRounds; ++u) {
-    const int t = t0 + 64 * u;
-    if (t >= n || (unsigned)c[u] >= (unsigned)kc) {  // a token without a valid cluster is left out
-      c[u] = -1;
-      if (a.token_row && t < n) a.token_row[r0 + t] = -1;
-    }
-  }
+  leave_out_invalid(a, c, t0, n, kc, r0);
   __syncthreads();
   uint16_t *const mine = tab + wave * a.bin_stride;
-  const int bits = n_bins > 1 ? 32 - __clz(n_bins - 1) : 0;
   int rank[kRankRounds];
-#pragma unroll
-  for (int u = 0; u < kRankRounds; ++u) {
-    const int bin = c[u] >> 4;
-    const bool live = c[u] >= 0;
-    uint64_t peers = __ballot(live);
-    for (int b = 0; b < bits; ++b) {
-      const bool bit = (bin >> b) & 1;
-      const uint64_t ones = __ballot(bit);
-      peers &= bit ? ones : ~ones;
-    }
-    const int before = live ? mine[bin] : 0;
-    const int ahead = __popcll(peers & lanes_below());
-    rank[u] = before + ahead;
-    wave_lds_order();
-    if (live && ahead == 0) mine[bin] = (uint16_t)(before + __popcll(peers));
-    wave_lds_order();
-  }
+  rank_in_bins(c, rank, mine, n_bins);
   __syncthreads();
   // per bin: exclusive prefix over the waves, in place; the block's count
   int32_t *row = a.hist + ((size_t)seg * a.n_blocks + blk) * a.bin_stride;
-  for (int i = tid; i < n_bins; i += kRankThreads) {
-    int run = 0;
-#pragma unroll
-    for (int w = 0; w < kRankWaves; ++w) {
-      const int v = tab[w * a.bin_stride + i];
-      tab[w * a.bin_stride + i] = (uint16_t)run;
-      run += v;
-    }
-    row[i] = run;
-  }
+  for (int i = tid; i < n_bins; i += kRankThreads) row[i] = prefix_over_waves<kRankWaves>(tab + i, a.bin_stride);
   __syncthreads();
   uint16_t *out = a.rank + (size_t)seg * a.max_rows + t0;
 #pragma unroll
@@ -163,11 +192,7 @@ __global__ __launch_bounds__(T) void build_scan_kernel(BuildArgs a) {
     carry += tot;
   }
   if (tid == 0 && a.max_rows > 0) start[n_bins] = carry;
-  // clusters beyond the host's bound received no token: they are reported empty
-  for (int i = a.max_kc + tid; i < kc_all; i += T) {
-    if (a.cluster_offsets) a.cluster_offsets[c0 + i] = carry;
-    if (a.cluster_sizes) a.cluster_sizes[c0 + i] = 0;
-  }
+  report_unbounded_empty<T>(a, c0, kc_all, carry, tid);
 }
 
 // The word of a token in its bin is 16 x token + cluster: 32 bits hold it for segments of less than kShortRows tokens.
@@ -213,61 +238,23 @@ __global__ __launch_bounds__(T) void build_sort_kernel(BuildArgs a) {
     for (int u = 0; u < R; ++u) c[u] = a.assignment[r0 + min(t0 + 64 * u, n - 1)];
   }
   for (int i = tid; i < kWaves * a.bin_stride / 2; i += T) s_words[i] = 0;
-#pragma unroll
-  for (int u = 0; u < R; ++u) {
-    const int t = t0 + 64 * u;
-    if (t >= n || (unsigned)c[u] >= (unsigned)kc) {  // a token without a valid cluster is left out
-      c[u] = -1;
-      if (a.token_row && t < n) a.token_row[r0 + t] = -1;
-    }
-  }
+  leave_out_invalid(a, c, t0, n, kc, r0);
   __syncthreads();
   uint16_t *const mine = tab + wave * a.bin_stride;
-  const int bits = n_bins > 1 ? 32 - __clz(n_bins - 1) : 0;
-#pragma unroll
-  for (int u = 0; u < R; ++u) {
-    const int bin = c[u] >> 4;
-    const bool live = c[u] >= 0;
-    uint64_t peers = __ballot(live);
-    rank[u] = 0;
-    if (peers == 0) continue;
-    for (int b = 0; b < bits; ++b) {
-      const bool bit = (bin >> b) & 1;
-      const uint64_t ones = __ballot(bit);
-      peers &= bit ? ones : ~ones;
-    }
-    const int before = live ? mine[bin] : 0;
-    const int ahead = __popcll(peers & lanes_below());
-    rank[u] = before + ahead;
-    wave_lds_order();
-    if (live && ahead == 0) mine[bin] = (uint16_t)(before + __popcll(peers));
-    wave_lds_order();
-  }
+  rank_in_bins(c, rank, mine, n_bins);
   __syncthreads();
   int32_t *start = a.bin_start + (size_t)seg * (a.bin_stride + 1);
   int carry = 0;
   for (int i0 = 0; i0 < n_bins; i0 += T) {
     const int i = i0 + tid;
-    int run = 0;
-    if (i < n_bins) {
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const int v = tab[w * a.bin_stride + i];
-        tab[w * a.bin_stride + i] = (uint16_t)run;
-        run += v;
-      }
-    }
+    const int run = i < n_bins ? prefix_over_waves<kWaves>(tab + i, a.bin_stride) : 0;
     int tot;
     const int ex = block_excl_scan<int, kWaves>(run, scr, tot);
     if (i < n_bins) start[i] = s_start[i] = carry + ex;
     carry += tot;
   }
   if (tid == 0) start[n_bins] = carry;
-  // clusters beyond the host's bound received no token: they are reported empty
-  for (int i = a.max_kc + tid; i < kc_all; i += T) {
-    if (a.cluster_offsets) a.cluster_offsets[c0 + i] = carry;
-    if (a.cluster_sizes) a.cluster_sizes[c0 + i] = 0;
-  }
+  report_unbounded_empty<T>(a, c0, kc_all, carry, tid);
   __syncthreads();
   uint32_t *out = static_cast<uint32_t *>(a.binned) + (size_t)seg * a.max_rows;
 #pragma unroll
