@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 # fp32 sums of up to 10^4 weighted values of size ~1 (weights sum to 1), the scores' own rounding (|x| <= 40: 40 x 2^-23)
 # above it; the bar that the other parity tests hold this path to as well
 TIGHT = 2e-4
+MOST_INLINE = 512  # a head that keeps this many rows or fewer may be attended by the workgroup that selects it
 
 
 def _whole(cache, exact_share=1.0, seed=0):
@@ -53,15 +54,15 @@ def test_split_decode_inside_the_selection_launch(heads, context):
     import paper_2602_05191_amd as dp
     n_seg = heads // 2
     ctx = [context + 61 * i for i in range(n_seg)]
-    ctx[0] = 1
     if n_seg > 3:
-        ctx[1], ctx[2] = 64, 65
+        ctx[0], ctx[1], ctx[2] = 1, 64, 65
     c = make_cache(batch=n_seg, n_kv_heads=1, n_q_heads=2, context=ctx, mean_cluster=7, size_hi=32, q_scale=0.4, seed=102)
     if n_seg > 3:
         c.cluster_sizes[int(c.seg_cluster_ptr[3]):int(c.seg_cluster_ptr[4])] = 0   # a segment with nothing in it
     orc = oracle.Oracle(c)
     for flags in (0, dp.DP_FLAG_SEPARATE_DECODE_LAUNCH):
         g = H.gpu_decode_attention(c, 1.0, 1.0, flags=flags)
+        assert (g.n_exact_tokens > MOST_INLINE).sum() >= (heads - 8 if n_seg > 3 else heads)
         H.check_outputs(c, orc, g, tight=TIGHT)
         again = H.gpu_decode_attention(c, 1.0, 1.0, flags=flags)
         assert np.array_equal(g.out.view(np.uint32), again.out.view(np.uint32))
@@ -70,14 +71,20 @@ def test_split_decode_inside_the_selection_launch(heads, context):
     H.check_outputs(c, orc, g, tight=TIGHT)
 
 
-@pytest.mark.parametrize("n", [70, 100, 300, 2000])
+@pytest.mark.parametrize("n", [70, 100, 300, MOST_INLINE + 3, MOST_INLINE + 65, 2000])
 def test_split_decode_keeps_an_infinite_value_in_its_dimension(n):
-    """An infinity in the segment's last V row, which the lanes without a row of their own name as well."""
+    """An infinity in the segment's last V row, which the lanes without a row of their own name as well.  Lists given by
+    the caller are never attended anywhere else; heads of a step are where they have more rows than their own workgroup
+    takes."""
     import paper_2602_05191_amd as dp
     c = make_cache(batch=1, n_kv_heads=1, n_q_heads=4, context=n, mean_cluster=8, size_hi=32, q_scale=0.3, seed=103)
     c.v_cache[n - 1, 5] = 0x7F80
+    outs = [H.gpu_sparse_decode(c, *_whole(c))[0]]
     for flags in (0, dp.DP_FLAG_SEPARATE_DECODE_LAUNCH):
-        out = H.gpu_decode_attention(c, 1.0, 1.0, flags=flags).out
+        g = H.gpu_decode_attention(c, 1.0, 1.0, flags=flags)
+        assert (g.n_exact_tokens == n).all()
+        outs.append(g.out)
+    for out in outs:
         assert np.isposinf(out[..., 5]).all() and np.isfinite(np.delete(out, 5, axis=-1)).all()
 
 
