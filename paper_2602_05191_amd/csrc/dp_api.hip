@@ -178,12 +178,16 @@ dp_status select_only(const dp_problem *problem, const float *logits, const dp::
 
 // Whether a step runs the split decode inside the selection launch.
 // Where the shared launch pays (measured, 32 heads, us per step against three launches): it saves the decode launch
-// of a step whose heads are all attended inline (8192 clusters per KV head: 13.5 against 15.2; 2048 clusters: 10.9
-// against 13.8), and it starts the queue without a launch in between when heads are flat (8192 clusters: one flat head
-// in eight 41.0 against 44.5, all of them 64.5 against 67.0; 2048 clusters: 28.3 against 27.5 and 41.1 against 41.1,
-// about level, so the peaked step decides there).  The flag below is for a caller who knows better.  With more heads than
-// kSameLaunchMaxHeads the selecting workgroups come in rounds and the shared launch loses (512 peaked heads: 29.6
-// against 24.3).  Top-p rule only (a fixed budget leaves rows on every head).
+// of a step whose heads are all attended inline (8192 clusters per KV head: 13.2 against 14.9; 2048 clusters: 10.4
+// against 12.4), and it starts the queue without a launch in between when heads are flat (8192 clusters: one flat head
+// in eight 41.0 against 44.4, all of them 64.0 both ways).  At 2048 clusters it loses on flat heads (28.5 against 27.8 and
+// 40.6 against 36.4); the host cannot tell them, and the peaked step decides.  The flag below is for a caller who knows
+// better.  With more heads than kSameLaunchMaxHeads the selecting workgroups come in rounds and the shared launch loses
+// (512 peaked heads: 29.6 against 24.3).
+// A fixed budget keeps three launches: where it leaves rows on the heads the shared launch gains nothing, or loses (a
+// fifth to a quarter of the clusters retained and 2 % exact, us per layer: three sequences of up to 30 k tokens, 96 heads,
+// 33.7 against 31.5, 32 heads over 2048 clusters 29.0 against 28.6, over 8192 44.5 against 45.2).  (A small one, 5 % and 0.5 % over 2048 clusters, or
+// any over 512, would gain up to 4 us per layer: 20.0 against 23.7, 18.6 against 22.1.)
 bool shares_launch(const dp_problem *problem, bool by_count) {
   const int mk = problem->max_clusters_per_seg;
   const int64_t nh = (int64_t)problem->batch * problem->n_q_heads;

@@ -27,9 +27,9 @@
 // load (lane t holds dims [8t, 8t+8) of K for the dot and of V for the
 // accumulation) and keeps its own online-softmax state in base-2 exponent form;
 // the states are merged through LDS at the end of the item.  (With the lists staged
-// in LDS for the whole workgroup and walked row by row: one 128 k-token step of 256
-// heads, half of them flat, 148 us for the decode launch against 136; a fixed budget,
-// 70 MB of rows, 27.3 against 24.3.)  Partials (m, l, acc[128]) go to the
+// in LDS for the whole workgroup and walked row by row the decode launch took 155 us
+// against 134 for 256 heads, half of them flat, over 128 k tokens, 765 MB of rows; and
+// 27.1 against 23.2 for a fixed budget, 70 MB of rows.)  Partials (m, l, acc[128]) go to the
 // workspace; the item of a head that finishes last (an arrival counter, no
 // waiting) merges them (log-sum-exp merge), normalises and writes the output.
 #pragma once
@@ -103,9 +103,10 @@ inline DecodeArgs decode_args_of(const CacheView &c, const int32_t *n_exact, con
 #define DP_LD_I32(lvalue) \
   (kCoherent ? __hip_atomic_load(&(lvalue), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (lvalue))
 
-// Rows in flight per 16-lane row in the queue.  Inside the selection's launch a CU holds one or two large
-// workgroups (16 waves at most, against 20 of the decode kernel's small ones): the rows in flight per wave are doubled
-// there (32 flat heads over 128 k tokens: 105 -> 98 us per step).
+// Rows in flight per 16-lane row in the queue.  Inside the selection's launch a CU holds one large workgroup (8 or 16 waves,
+// against 20 of the decode kernel's small ones): the rows in flight per wave are doubled there (at 4 / at 8, 32 flat heads
+// over 32 k tokens, four layers 141.2 / 137.5 us; over 128 k, one head in eight flat, two layers 86.5 / 85.8, all of them
+// flat 140.0 both).
 __host__ __device__ constexpr int queue_batch(bool coherent) { return coherent ? 8 : kAttendBatch; }
 
 // rows per item of a head with R rows (multiple of kChunkRows); g: least chunks per item of this launch

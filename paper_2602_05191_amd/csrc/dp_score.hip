@@ -328,8 +328,11 @@ hipError_t launch_score(const CacheView &c, float *logits, hipStream_t s, hipEve
     // 59.4 / 58.0; 8 of 7 k, 2.1 MiB: 39.9 / 40.4 and 47.1 / 47.2).  Above 24 MiB, one layer that is scored again and again
     // out of the caches loses (32 MiB, G = 1: 12.3 / 12.95), which the host cannot tell from a step's layers.  A group that
     // takes two passes (G = 3) reads its centroids again at once: warm 16 MiB 64.5 / 67.0 and 32 MiB 79.5 / 86.8 over 4
-    // layers, with only the last pass non-temporal no gain either (cold 75.5 / 75.6).  (Flat heads read centroids again as
-    // pseudo-tokens and lose up to 1.5 %: 16 MiB, 2 layers cold 164.2 / 166.6.)
+    // layers, with only the last pass non-temporal no gain either (cold 75.5 / 75.6).  Steps with flat heads,
+    // which read centroids again as pseudo-tokens, lose 1 to 2 % warm and gain as much cold (16 sequences of
+    // 2.5 k tokens, 4.9 MiB, half of the heads flat, 8 layers 306.4 / 310.9 and 354.1 / 351.3; 8 x 4096 clusters, one head in
+    // eight flat, 8 layers 263.5 / 267.9 and 310.7 / 303.4), except where the rule begins (8 x 2048, one in eight, 8 layers
+    // 214.3 / 218.6 and 254.8 / 264.1), which is kept for the peaked ones (32 layers cold 468.4 / 459.8).
     const int64_t bytes = (int64_t)c.total_clusters * kRowBytes;
     const bool stream = c.group != 3 && bytes >= (4 << 20) && bytes <= (24 << 20);
     int h0 = 0;
