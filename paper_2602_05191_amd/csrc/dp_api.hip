@@ -186,8 +186,8 @@ dp_status select_only(const dp_problem *problem, const float *logits, const dp::
 // (512 peaked heads: 29.6 against 24.3).
 // A fixed budget keeps three launches: where it leaves rows on the heads the shared launch gains nothing, or loses (a
 // fifth to a quarter of the clusters retained and 2 % exact, us per layer: three sequences of up to 30 k tokens, 96 heads,
-// 33.7 against 31.5, 32 heads over 2048 clusters 29.0 against 28.6, over 8192 44.5 against 45.2).  (A small one, 5 % and 0.5 % over 2048 clusters, or
-// any over 512, would gain up to 4 us per layer: 20.0 against 23.7, 18.6 against 22.1.)
+// 33.7 against 31.5, 32 heads over 2048 clusters 29.0 against 28.6, over 8192 44.5 against 45.2).  (A small one, 5 % and
+// 0.5 % over 2048 clusters, or any over 512, would gain up to 4 us per layer: 20.0 against 23.7, 18.6 against 22.1.)
 bool shares_launch(const dp_problem *problem, bool by_count) {
   const int mk = problem->max_clusters_per_seg;
   const int64_t nh = (int64_t)problem->batch * problem->n_q_heads;
