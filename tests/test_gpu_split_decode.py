@@ -129,3 +129,15 @@ def test_flat_heads_around_the_rows_their_own_workgroup_attends(p1, fewest, most
     rows = np.array([t + len(a) for t, a in zip(g.n_exact_tokens, g.approx)])
     assert fewest < rows.min() and rows.max() < most, rows
     H.check_outputs(c, oracle.Oracle(c, sm_scale=0.02), g, tight=TIGHT)
+
+
+@pytest.mark.parametrize("n", [128, 449, 512, 513, 640])
+@pytest.mark.parametrize("lo, hi", [(0, 0), (0, 64), (64, 128)])
+def test_split_decode_merges_few_and_many_partials(n, lo, hi):
+    """Items of 64 rows in a launch this light: 2, 8, 9 and 10 partials, one of them without any weight (every row of it
+    scores -inf)."""
+    c = make_cache(batch=1, n_kv_heads=1, n_q_heads=2, context=n, mean_cluster=1, size_lo=1, size_hi=1, q_scale=0.4, seed=108)
+    if hi > lo:
+        c.q[..., 7] = 0x3F80
+        c.k_cache[lo:hi, 7] = 0xFF80
+    _check_sets(c, *_whole(c))
